@@ -210,40 +210,39 @@ __global__ void tubelet_pack_kernel(const ReqDesc* __restrict__ reqs, int nreq_,
 
 // Bias (and, for FP8 operands, row-scale x activation-scale) values of the
 // output features one lane's accumulators hold: features
-// n0 + wn BN/2 + 32 ns + 8 g + 4 half + e.  Fetched as 16-byte vectors
-// (bias and scales are 16-byte aligned) all at once, early, instead of once
-// per group of four inside the epilogue.
-template <int BN>
+// n0 + 32 (wn NS + ns) + 8 g + 4 half + e for the wave's NS subtiles of 32.
+// Fetched as 16-byte vectors (bias and scales are 16-byte aligned) all at
+// once, early, instead of once per group of four inside the epilogue.
+template <int NS>
 struct EpiCols {
-  f32x4 b[BN / 64][4], s[BN / 64][4];
+  f32x4 b[NS][4], s[NS][4];
 };
-template <class Op, int BN>
-__device__ __forceinline__ void epi_load_cols(const GemmArgs& a, int n0, int wn, int half, EpiCols<BN>& c) {
+template <class Op, int NS>
+__device__ __forceinline__ void epi_load_cols(const GemmArgs& a, int n0, int wn, int half, EpiCols<NS>& c) {
   constexpr bool SC = sizeof(typename Op::T) == 1;
   const float xsc = SC ? *a.xscale : 1.0f;
 #pragma unroll
-  for (int ns = 0; ns < BN / 64; ++ns)
+  for (int ns = 0; ns < NS; ++ns)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const int n = n0 + wn * (BN / 2) + ns * 32 + g * 8 + half * 4;
+      const int n = n0 + (wn * NS + ns) * 32 + g * 8 + half * 4;
       c.b[ns][g] = *reinterpret_cast<const f32x4*>(a.bias + n);
       if constexpr (SC) c.s[ns][g] = *reinterpret_cast<const f32x4*>(a.wscale + n) * xsc;
     }
 }
 
-// Epilogue of one 128 x BN tile straight from the accumulators (the head's
-// unpatchify scatter), for the tile's rows below Mlive.
-template <class Op, int BN, int EPI, class OutT>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[BN / 64][2], int m0, int n0,
-                                              int Mlive, int nreq, int lane, int wave, const EpiCols<BN>& cols) {
-  constexpr int NSUB = BN / 64;
+// Epilogue straight from the accumulators (the head's unpatchify scatter),
+// for the tile's rows below Mlive: the wave at (wn, wm) holds NS x MS
+// subtiles of 32 features x 32 tokens.
+template <class Op, int EPI, class OutT, int NS, int MS>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NS][MS], int m0, int n0, int Mlive,
+                                              int nreq, int lane, int wn, int wm, const EpiCols<NS>& cols) {
   constexpr bool SC = sizeof(typename Op::T) == 1;  // FP8 operands carry row scales
   const int half = lane >> 5, l32 = lane & 31;
-  const int wn = wave >> 1, wm = wave & 1;
   const float oinv = a.out_scale ? 1.0f / *a.out_scale : 1.0f;
 #pragma unroll
-  for (int ms = 0; ms < 2; ++ms) {
-    const int m = m0 + wm * 64 + ms * 32 + l32;
+  for (int ms = 0; ms < MS; ++ms) {
+    const int m = m0 + (wm * MS + ms) * 32 + l32;
     if (m >= Mlive) continue;
     int r = 0, tj = 0, ty = 0, tx = 0;
     if (EPI == EPI_PE) {
@@ -260,10 +259,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[B
       ty = p / d.gx; tx = p - ty * d.gx;
     }
 #pragma unroll
-    for (int ns = 0; ns < NSUB; ++ns) {
+    for (int ns = 0; ns < NS; ++ns) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int n = n0 + wn * (BN / 2) + ns * 32 + g * 8 + half * 4;
+        const int n = n0 + (wn * NS + ns) * 32 + g * 8 + half * 4;
         float v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -340,31 +339,29 @@ constexpr int epi_stage_bytes() {
 // instruction covers contiguous row segments instead of one short piece per
 // token.  The V part of the QKV product is staged transposed and written as
 // contiguous token runs of V^T.  smem must hold epi_stage_bytes<BN, OutT, BM_>().
-// The tile is BM_ tokens x BN features over 2 WM_ waves, wave w covering
-// tokens (w % WM_) 64 .. +63 and features (w / WM_) BN/2 .. +BN/2-1.
-template <class Op, int BN, int EPI, class OutT, int BM_ = BM, int WM_ = 2>
-__device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (&acc)[BN / 64][2], int m0, int n0,
-                                                     int Mlive, int nreq, int tid, uint8_t* smem,
-                                                     const EpiCols<BN>& cols, bool active = true) {
-  constexpr int NT_ = 128 * WM_;
-  constexpr int NSUB = BN / 64;
+// The tile is BM_ tokens x BN features; the wave at (wn, wm) holds NS x MS
+// subtiles of 32 features x 32 tokens.  Waves without a part of the tile
+// (!active, the other k groups of a split) only join the barriers and the
+// row stores, which all NT_ threads of the workgroup share.
+template <class Op, int BN, int EPI, class OutT, int BM_, int NT_, int NS, int MS>
+__device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (&acc)[NS][MS], int m0, int n0,
+                                                     int Mlive, int nreq, int tid, int wn, int wm, uint8_t* smem,
+                                                     const EpiCols<NS>& cols, bool active = true) {
   constexpr int TPB = BN * (int)sizeof(OutT) + 16;   // row pitch (bytes), row-major tile
   constexpr int TPV = BM_ * (int)sizeof(OutT) + 16;  // row pitch (bytes), transposed V tile
   constexpr int EO = 16 / (int)sizeof(OutT);          // output elements per 16-byte chunk
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
   const int half = lane >> 5, l32 = lane & 31;
-  const int wn = wave / WM_, wm = wave % WM_;
   const float oinv = a.out_scale ? 1.0f / *a.out_scale : 1.0f;
   const int D = EPI == EPI_QKV ? a.heads * 64 : 1;
   const int part = EPI == EPI_QKV ? n0 / D : 0;  // tiles never straddle Q | K | V
   const bool vtile = EPI == EPI_QKV && part == 2;
   constexpr bool SC = sizeof(typename Op::T) == 1;  // FP8 operands carry row scales
   __syncthreads();  // every wave is done with the operand tiles
-  // (threads beyond the tile's 2 WM_ waves, !active, only join the barriers)
   if (active) {
 #pragma unroll
-  for (int ms = 0; ms < 2; ++ms) {
-    const int ml = wm * 64 + ms * 32 + l32;
+  for (int ms = 0; ms < MS; ++ms) {
+    const int ml = (wm * MS + ms) * 32 + l32;
     const int m = m0 + ml;
     int r = 0, tj = 0, ty = 0, tx = 0;
     if (EPI == EPI_PE) {
@@ -376,10 +373,10 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (
       ty = p / d.gx; tx = p - ty * d.gx;
     }
 #pragma unroll
-    for (int ns = 0; ns < NSUB; ++ns) {
+    for (int ns = 0; ns < NS; ++ns) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int nl = wn * (BN / 2) + ns * 32 + g * 8 + half * 4;
+        const int nl = (wn * NS + ns) * 32 + g * 8 + half * 4;
         const int n = n0 + nl;
         float v[4];
 #pragma unroll
@@ -419,7 +416,6 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (
   }
   }
   __syncthreads();
-  if (!active) return;
   if (vtile) {
     // V^T rows: EO consecutive columns per 16-byte chunk; a 2-byte chunk
     // can hold permuted tokens up to the end of its group of 16 (a 1-byte
@@ -521,15 +517,10 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (
   }
 }
 
-// KS = 2 (FP32 products of at most one workgroup per CU): 8 waves, the
-// second four taking the second half of every stage's k steps into
-// accumulators of their own, added to the first four's through LDS before
-// the epilogue, so each SIMD holds two waves
-template <class Op, int BN, int EPI, int XM, class OutT, int KS = 1>
-__global__ __launch_bounds__(NT * KS, KS == 1 ? 2 : 1) void gemm_kernel(const GemmArgs a) {
+template <class Op, int BN, int EPI, int XM, class OutT>
+__global__ __launch_bounds__(NT, 2) void gemm_kernel(const GemmArgs a) {
   typedef typename Op::T T;
-  static_assert(KS == 1 || (KS == 2 && EPI != EPI_HEAD), "K split: staged epilogues only");
-  constexpr int NT_ = NT * KS;
+  constexpr int NT_ = NT;
   constexpr int BK = Op::BK;
   constexpr int E = 16 / sizeof(T);               // elements per 16-byte chunk
   constexpr int CPR = BK * sizeof(T) / 16;        // chunks per stage row
@@ -636,18 +627,16 @@ __global__ __launch_bounds__(NT * KS, KS == 1 ? 2 : 1) void gemm_kernel(const Ge
       *reinterpret_cast<uint4*>(&ws[buf_][c_row[i] * PITCH + c_k[i]]) = WR[i];                               \
   } while (0)
 
-  // waves 4..7 (KS = 2) repeat waves 0..3's tile positions on the other k steps
-  const int wq = wave & 3, kgrp = KS == 1 ? 0 : wave >> 2;
-  const int wn = wq >> 1, wm = wq & 1;
-  static_assert(STEPS % (KS * G) == 0, "whole LDS reads per k group");
+  const int wn = wave >> 1, wm = wave & 1;
+  static_assert(STEPS % G == 0, "whole LDS reads");
   f32x16 acc[NSUB][2];
 #pragma unroll
   for (int i = 0; i < NSUB; ++i) { acc[i][0] = f32x16{}; acc[i][1] = f32x16{}; }
 
   // one K stage from LDS buffer buf_ into the accumulators
 #define REVO_GEMM_COMPUTE(buf_)                                                                              \
-  _Pragma("unroll") for (int s0 = 0; s0 < STEPS / KS; s0 += G) {                                            \
-    const int koff = half * (BK / 2) + (kgrp * (STEPS / KS) + s0) * Op::KPL;                                 \
+  _Pragma("unroll") for (int s0 = 0; s0 < STEPS; s0 += G) {                                                 \
+    const int koff = half * (BK / 2) + s0 * Op::KPL;                                                         \
     if constexpr (FB == 32) {                                                                                \
       uint4 wf[NSUB][2], xf[2][2];                                                                           \
       _Pragma("unroll") for (int ns = 0; ns < NSUB; ++ns) {                                                  \
@@ -703,39 +692,14 @@ __global__ __launch_bounds__(NT * KS, KS == 1 ? 2 : 1) void gemm_kernel(const Ge
 #undef REVO_GEMM_STORE
 #undef REVO_GEMM_COMPUTE
 
-  if constexpr (KS == 2) {
-    // the second k group's accumulators into the first's, lane by lane
-    // (identical fragment layouts), through the operand stages' LDS
-    static_assert(4 * NSUB * 2 * 16 * 64 * 4 <= (OPB > EPB ? OPB : EPB), "reduction fits the stages");
-    float* red = reinterpret_cast<float*>(smem);
-    __syncthreads();  // every wave is done with the operand stages
-    if (kgrp == 1) {
-#pragma unroll
-      for (int ns = 0; ns < NSUB; ++ns)
-#pragma unroll
-        for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) red[(((wq * NSUB + ns) * 2 + ms) * 16 + j) * 64 + lane] = acc[ns][ms][j];
-    }
-    __syncthreads();
-    if (kgrp == 0) {
-#pragma unroll
-      for (int ns = 0; ns < NSUB; ++ns)
-#pragma unroll
-        for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) acc[ns][ms][j] += red[(((wq * NSUB + ns) * 2 + ms) * 16 + j) * 64 + lane];
-    }
-  }
-  const bool act = kgrp == 0;
   // bias (and scale) vectors fetched together after the K loop: this
   // kernel has no registers to hold them through it
-  EpiCols<BN> cols;
-  epi_load_cols<Op, BN>(a, n0, wn, half, cols);
+  EpiCols<NSUB> cols;
+  epi_load_cols<Op, NSUB>(a, n0, wn, half, cols);
   if constexpr (EPI == EPI_HEAD) {
-    gemm_epilogue<Op, BN, EPI, OutT>(a, acc, m0, n0, Mlive, nreq, lane, wave, cols);
+    gemm_epilogue<Op, EPI, OutT, NSUB, 2>(a, acc, m0, n0, Mlive, nreq, lane, wn, wm, cols);
   } else {
-    gemm_epilogue_staged<Op, BN, EPI, OutT>(a, acc, m0, n0, Mlive, nreq, tid, smem, cols, act);
+    gemm_epilogue_staged<Op, BN, EPI, OutT, BM, NT_, NSUB, 2>(a, acc, m0, n0, Mlive, nreq, tid, wn, wm, smem, cols);
   }
 }
 
@@ -870,8 +834,8 @@ __global__ __launch_bounds__(128 * WM_, 512 / (128 * WM_)) void gemm_dma_kernel(
   f32x16 acc[BN / 64][2];
 #pragma unroll
   for (int i = 0; i < BN / 64; ++i) { acc[i][0] = f32x16{}; acc[i][1] = f32x16{}; }
-  EpiCols<BN> cols;  // in flight during the K loop
-  epi_load_cols<Op, BN>(a, n0, wn, half, cols);
+  EpiCols<BN / 64> cols;  // in flight during the K loop
+  epi_load_cols<Op, BN / 64>(a, n0, wn, half, cols);
 
   // stage k goes to buffer k % NS; loads past the last stage re-read it
   // into a free buffer, which keeps the wait counts static
@@ -893,7 +857,265 @@ __global__ __launch_bounds__(128 * WM_, 512 / (128 * WM_)) void gemm_dma_kernel(
   }
   wait_vm<0>();  // no load still writes LDS when the epilogue reuses it
 #undef REVO_GD_FETCH
-  gemm_epilogue_staged<Op, BN, EPI, OutT, BM_, WM_>(a, acc, m0, n0, Mlive, nreq, tid, stg, cols);
+  gemm_epilogue_staged<Op, BN, EPI, OutT, BM_, 128 * WM_, BN / 64, 2>(a, acc, m0, n0, Mlive, nreq, tid, wn, wm, stg,
+                                                                      cols);
+}
+
+// ---------------------------------------------------------------------------
+// Dense FP32 form on the BF16 matrix cores.  An FP32 value is exactly the sum
+// of three BF16 values (common.h split3), and the six largest of the nine
+// products of two such triples (all but x2 w3, x3 w2 and x3 w3, together at
+// most 2^-26 of |x w|) go into FP32 accumulators: 6 products at 16 times the
+// rate of the FP32 MFMA.  What bounds it at large sizes is the matrix cores:
+// 171 - 179 TFLOP/s at 43200 rows are 1030 - 1070 TFLOP/s of BF16 products,
+// where a large BF16 product of the library reaches 1263 (FP32 MFMA: 114 -
+// 125 TFLOP/s before, 154 for a large library product).  Its error against 64
+// bits is no larger: 2.9e-7 relative (K = 384) and 6.0e-7 (1536) with one k
+// group, 3.5e-7 and 7.0e-7 before; with two groups 2.1e-7 and 4.2e-7, 2.5e-7
+// and 5.0e-7 before.  Operand stages of BK values per row are fetched into
+// registers two stages ahead, split once per element on the way into LDS (one
+// BF16 plane per part), and read from there as 16-byte fragments.
+//
+// The BF16 MFMA flushes subnormal operands, so both operands are scaled by
+// 2^24 first: every bit of a scaled value is then at least 2^-125 and no part
+// of it is subnormal.  The accumulators hold 2^48 times the product.  A
+// non-finite operand, one too large for the scaled split, or an accumulator
+// past 2^80 makes the outputs it feeds non-finite; a wave that ends with such
+// an accumulator repeats its part with FP32 MFMAs from global memory, so the
+// result is what FP32 products give.
+
+// byte of 16-byte chunk c of row r in a plane with rows of BK BF16 values
+template <int BK>
+__device__ __forceinline__ int f32_swz(int r, int c) {
+  static_assert(BK == 32 || BK == 64, "rows of 64 or 128 bytes");
+  return BK == 32 ? r * 64 + ((c ^ ((r >> 2) & 3)) << 4) : gswz(r, c);
+}
+
+// Tile BM_ tokens x BN features; KG groups of WM_ x WN_ waves share out the 16-deep
+// k steps of every stage (their accumulators are added through LDS before the
+// epilogue); LB LDS buffers.
+template <int BM_, int BN, int WM_, int WN_, int KG, int BK, int LB, int EPI>
+__global__ __launch_bounds__(64 * WM_* WN_* KG, 2) void gemm_f32_kernel(const GemmArgs a) {
+  constexpr int NT_ = 64 * WM_ * WN_ * KG;
+  constexpr int MS = BM_ / (32 * WM_), NS = BN / (32 * WN_);
+  constexpr int CPR = BK / 4;                 // 16-byte global chunks per stage row
+  constexpr int XC = BM_ * CPR / NT_, WC = BN * CPR / NT_;
+  static_assert(XC * NT_ == BM_ * CPR && WC * NT_ == BN * CPR, "whole chunks per thread");
+  constexpr int STEPS = BK / 16 / KG;         // k steps per wave and stage
+  static_assert(STEPS * KG * 16 == BK, "whole k steps per group");
+  constexpr int XP = BM_ * BK * 2, WP = BN * BK * 2;  // bytes per plane
+  constexpr int SB = 3 * (XP + WP);
+  constexpr int EPB = EPI == EPI_HEAD ? 0 : epi_stage_bytes<BN, float, BM_>();
+  constexpr int RDB = (KG - 1) * WM_ * WN_ * NS * MS * 4096;
+  constexpr int LDSB = LB * SB > EPB ? (LB * SB > RDB ? LB * SB : RDB) : (EPB > RDB ? EPB : RDB);
+  __shared__ __attribute__((aligned(16))) uint8_t smem[LDSB];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, l32 = lane & 31;
+  // XCD-aware tile order, as in gemm_kernel
+  const int gn = a.N / BN;
+  const int ntiles = gridDim.x;
+  const int L = blockIdx.x;
+  const int xcd = L & 7, per = ntiles >> 3, rem = ntiles & 7;
+  const int tile = xcd * per + (xcd < rem ? xcd : rem) + (L >> 3);
+  const int m0 = (tile / gn) * BM_;
+  const int n0 = (tile - (tile / gn) * gn) * BN;
+  const int Mlive = a.dyn_m ? *a.dyn_m : a.M;
+  const int nreq = a.dyn_nreq ? *a.dyn_nreq : a.nreq;
+  if (m0 >= Mlive) return;
+  const int KT = a.K / BK;
+  const int wq = wave % (WM_ * WN_), kgrp = wave / (WM_ * WN_);
+  const int wn = wq / WM_, wm = wq % WM_;
+
+  const __amdgpu_buffer_rsrc_t wrs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.W, (short)0, a.N * a.K * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xrs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.X, (short)0, Mlive * a.K * 4, 0x00020000);
+  // chunk i of this thread: row (tid + i NT_) / CPR, values 4 ((tid + i NT_) %
+  // CPR) ..; NT_ / CPR is a multiple of 8, so only the row differs between i
+  const int crow = tid / CPR, ccol = tid % CPR;
+  constexpr int RSTEP = NT_ / CPR;
+  const int xo = ((m0 + crow) * a.K + ccol * 4) * 4, wo = ((n0 + crow) * a.K + ccol * 4) * 4;
+  const int rstep = RSTEP * a.K * 4;
+  int sto[XC > WC ? XC : WC];  // byte of the chunk's 8-byte piece in a plane
+#pragma unroll
+  for (int i = 0; i < (XC > WC ? XC : WC); ++i) sto[i] = f32_swz<BK>(crow + i * RSTEP, ccol >> 1) + (ccol & 1) * 8;
+
+  float4 xr0[XC], wr0[WC], xr1[XC], wr1[WC];
+#define REVO_GF_LOAD(kt_, XR, WR)                                                                              \
+  do {                                                                                                         \
+    const int kb_ = (kt_) * (BK * 4);                                                                          \
+    _Pragma("unroll") for (int i = 0; i < XC; ++i) XR[i] =                                                     \
+        __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xo + i * rstep, kb_, 0));        \
+    _Pragma("unroll") for (int i = 0; i < WC; ++i) WR[i] =                                                     \
+        __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(wrs, wo + i * rstep, kb_, 0));        \
+  } while (0)
+#define REVO_GF_STORE(buf_, XR, WR)                                                                            \
+  do {                                                                                                         \
+    uint8_t* xs_ = smem + (buf_) * SB;                                                                         \
+    uint8_t* ws_ = xs_ + 3 * XP;                                                                               \
+    _Pragma("unroll") for (int i = 0; i < XC; ++i) {                                                           \
+      uint2 p[3];                                                                                              \
+      split3x4(XR[i], p);                                                                                      \
+      _Pragma("unroll") for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(xs_ + j * XP + sto[i]) = p[j];   \
+    }                                                                                                          \
+    _Pragma("unroll") for (int i = 0; i < WC; ++i) {                                                           \
+      uint2 p[3];                                                                                              \
+      split3x4(WR[i], p);                                                                                      \
+      _Pragma("unroll") for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(ws_ + j * WP + sto[i]) = p[j];   \
+    }                                                                                                          \
+  } while (0)
+
+  f32x16 acc[NS][MS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+#pragma unroll
+    for (int j = 0; j < MS; ++j) acc[i][j] = f32x16{};
+
+  auto compute = [&](int buf) {
+    const uint8_t* xs = smem + buf * SB;
+    const uint8_t* ws = xs + 3 * XP;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      const int c = 2 * (kgrp * STEPS + s) + half;
+      bf16x8 wf[3][NS], xf[3][MS];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+#pragma unroll
+        for (int ns = 0; ns < NS; ++ns)
+          wf[j][ns] = *reinterpret_cast<const bf16x8*>(ws + j * WP + f32_swz<BK>((wn * NS + ns) * 32 + l32, c));
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+          xf[j][ms] = *reinterpret_cast<const bf16x8*>(xs + j * XP + f32_swz<BK>((wm * MS + ms) * 32 + l32, c));
+      }
+      // smallest products first
+#pragma unroll
+      for (int p = 0; p < 6; ++p) {
+        constexpr int PW[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+        for (int ns = 0; ns < NS; ++ns)
+#pragma unroll
+          for (int ms = 0; ms < MS; ++ms) OpBF16::mma(acc[ns][ms], wf[PW[p]][ns], xf[PX[p]][ms]);
+      }
+    }
+  };
+
+  // (prefetches past the last stage re-read it; those copies are never used)
+  REVO_GF_LOAD(0, xr0, wr0);
+  REVO_GF_LOAD(KT > 1 ? 1 : 0, xr1, wr1);
+  if constexpr (LB == 2) {
+    REVO_GF_STORE(0, xr0, wr0);
+    __syncthreads();
+    for (int kt = 0; kt < KT; kt += 2) {
+      REVO_GF_LOAD(kt + 2 < KT ? kt + 2 : KT - 1, xr0, wr0);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(0);
+      if (kt + 1 >= KT) break;
+      REVO_GF_STORE(1, xr1, wr1);
+      __syncthreads();
+      REVO_GF_LOAD(kt + 3 < KT ? kt + 3 : KT - 1, xr1, wr1);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(1);
+      if (kt + 2 >= KT) break;
+      REVO_GF_STORE(0, xr0, wr0);
+      __syncthreads();
+    }
+  } else {
+    for (int kt = 0; kt < KT; kt += 2) {
+      REVO_GF_STORE(0, xr0, wr0);
+      __syncthreads();
+      REVO_GF_LOAD(kt + 2 < KT ? kt + 2 : KT - 1, xr0, wr0);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(0);
+      if (kt + 1 >= KT) break;
+      __syncthreads();
+      REVO_GF_STORE(0, xr1, wr1);
+      __syncthreads();
+      REVO_GF_LOAD(kt + 3 < KT ? kt + 3 : KT - 1, xr1, wr1);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(0);
+      if (kt + 2 >= KT) break;
+      __syncthreads();
+    }
+  }
+#undef REVO_GF_LOAD
+#undef REVO_GF_STORE
+
+  // non-finite accumulators: this wave's part again in FP32 products, over
+  // the same values of k (its group's steps of every stage)
+  {
+    float t = 0.0f;
+#pragma unroll
+    for (int ns = 0; ns < NS; ++ns)
+#pragma unroll
+      for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t = fmaf(acc[ns][ms][j], 0.0f, t);
+    if (__any(t != 0.0f)) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int j = 0; j < MS; ++j) acc[i][j] = f32x16{};
+#pragma unroll 1
+      for (int i = 0; i < KT * STEPS * 8; ++i) {
+        const int st = i / (STEPS * 8);
+        const int k = st * BK + kgrp * STEPS * 16 + 2 * (i - st * (STEPS * 8));
+        float xv[MS];
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+          xv[ms] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                       xrs, ((m0 + (wm * MS + ms) * 32 + l32) * a.K + k + half) * 4, 0, 0));
+#pragma unroll
+        for (int ns = 0; ns < NS; ++ns) {
+          const float wv = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                               wrs, ((n0 + (wn * NS + ns) * 32 + l32) * a.K + k + half) * 4, 0, 0));
+#pragma unroll
+          for (int ms = 0; ms < MS; ++ms) OpF32::mma(acc[ns][ms], wv, xv[ms]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int ns = 0; ns < NS; ++ns)
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms) acc[ns][ms] *= 0x1p-48f;
+    }
+  }
+
+  if constexpr (KG > 1) {
+    // the other groups' accumulators into the first's, lane by lane
+    // (identical fragment layouts), through the operand stages' LDS
+    float* red = reinterpret_cast<float*>(smem);
+    __syncthreads();  // every wave is done with the operand stages
+    if (kgrp > 0) {
+#pragma unroll
+      for (int ns = 0; ns < NS; ++ns)
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+          for (int j = 0; j < 16; ++j)
+            red[(((((kgrp - 1) * WM_ * WN_ + wq) * NS + ns) * MS + ms) * 16 + j) * 64 + lane] = acc[ns][ms][j];
+    }
+    __syncthreads();
+    if (kgrp == 0) {
+#pragma unroll
+      for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+        for (int ns = 0; ns < NS; ++ns)
+#pragma unroll
+          for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+              acc[ns][ms][j] += red[((((g * WM_ * WN_ + wq) * NS + ns) * MS + ms) * 16 + j) * 64 + lane];
+    }
+  }
+  EpiCols<NS> cols;
+  epi_load_cols<OpF32, NS>(a, n0, wn, half, cols);
+  if constexpr (EPI == EPI_HEAD) {
+    if (kgrp == 0) gemm_epilogue<OpF32, EPI, float, NS, MS>(a, acc, m0, n0, Mlive, nreq, lane, wn, wm, cols);
+  } else {
+    gemm_epilogue_staged<OpF32, BN, EPI, float, BM_, NT_, NS, MS>(a, acc, m0, n0, Mlive, nreq, tid, wn, wm, smem, cols,
+                                                                  kgrp == 0);
+  }
 }
 
 template <class Op, int EPI, int XM, class OutT>
@@ -923,18 +1145,33 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   if constexpr (RING && sizeof(typename Op::T) == 2) {
     return -22;  // not reached: every BF16 dense product takes the ring
   } else {
-    // the gather loader's per-row token coordinates leave no registers for a
-    // 128-wide tile with two prefetched stages.  Dense products take 128-wide
-    // tiles unless 64-wide ones (twice as many, half the work each) spread
-    // better over the 256 CUs: the busiest CU then holds fewer feature columns
-    if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4 && EPI != EPI_HEAD) {
-      // FP32 products of at most one 64-wide workgroup per CU: eight waves
-      // that split each stage's k steps, two per SIMD instead of one
-      if ((long long)gm * (a.N / 64) <= 256) {
-        gemm_kernel<Op, 64, EPI, XM, OutT, 2><<<gm * (a.N / 64), 2 * NT, 0, s>>>(a);
-        return hipGetLastError() == hipSuccess ? 0 : -5;
-      }
+    if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4) {
+      // Four tile forms, by how many tiles they give the 256 CUs (us on one
+      // box for M x N x K, with the FP32-MFMA kernel these replace first):
+      //  64 x 32, 8 waves in 4 k groups, while its tiles are at most one per
+      //   CU (latency: 576 x 384 x 1536 54.0 -> 18.6; 64 x 64 26.3);
+      //  128 x 64, 8 waves in 2 k groups, from 160 to 256 tiles, about one per
+      //   CU (4608 x 384 x 1536 56.6 -> 43.1; 64 x 64 45.2, 128 x 128 81.8);
+      //  64 x 64, 8 waves in 2 k groups, up to 700 tiles (2304 x 1152 x 384
+      //   31.2 -> 18.9; 128 x 64 21.2, 128 x 128 25.4);
+      //  128 x 128, 4 waves, from 384 tiles (43200 x 1536 x 384 445 -> 298;
+      //   128 x 64 339), and 128 x 64 in between (10800 x 384 x 1536 109 -> 80;
+      //   128 x 128 87)
+      const long long gm64 = cdiv(a.M, 64);
+      const long long t6432 = gm64 * (a.N / 32), t6464 = gm64 * (a.N / 64), t12864 = (long long)gm * (a.N / 64);
+      const long long t128 = a.N % 128 == 0 ? (long long)gm * (a.N / 128) : 0;
+      if (t6432 <= 256 && a.K % 64 == 0)
+        gemm_f32_kernel<64, 32, 2, 1, 4, 64, 2, EPI><<<(unsigned)t6432, 512, 0, s>>>(a);
+      else if (t6464 <= 700 && !(t12864 >= 160 && t12864 <= 256))
+        gemm_f32_kernel<64, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t6464, 512, 0, s>>>(a);
+      else if (t128 >= 384)
+        gemm_f32_kernel<128, 128, 2, 2, 1, 32, 1, EPI><<<(unsigned)t128, 256, 0, s>>>(a);
+      else
+        gemm_f32_kernel<128, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t12864, 512, 0, s>>>(a);
+      return hipGetLastError() == hipSuccess ? 0 : -5;
     }
+    // the gather loader's per-row token coordinates leave no registers for a
+    // 128-wide tile with two prefetched stages
     if constexpr (XM == X_DENSE) {
       const long long t128 = (long long)gm * (a.N / 128);
       const bool wide = a.N % 128 == 0 && (2 * t128 + 255) / 256 >= 2 * ((t128 + 255) / 256);

@@ -63,6 +63,74 @@ def test_linear(prec, M, N, K, epi):
     assert np.all(np.abs(got - ref) <= tol + 1e-7), float(np.abs(got - ref).max())
 
 
+# One shape on each side of the lines between the FP32 tile forms (64 x 32,
+# 64 x 64, 128 x 64 and 128 x 128), K of an odd number of 32-value stages
+# (which the 64-value stages of the 64 x 32 form do not take), ragged rows
+@pytest.mark.parametrize("M,N,K", [(63, 64, 96), (65, 64, 64), (1365, 384, 192), (1366, 384, 192), (1344, 384, 96), (3393, 384, 32),
+                                   (7460, 384, 64), (3968, 1536, 64), (4097, 1536, 160), (20001, 64, 64)])
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_linear_fp32_tile_forms(M, N, K, epi):
+    x = RNG.standard_normal((M, K))
+    w = RNG.standard_normal((N, K)) * math.sqrt(2.0 / K)
+    b = 0.1 * RNG.standard_normal(N)
+    xd, x64 = _as_op(x, FP32)
+    wd, w64 = _as_op(w, FP32)
+    bd = torch.tensor(b, dtype=torch.float32).cuda()
+    ref = oracle.linear(x64, w64, bd.double().cpu().numpy())
+    out = torch.zeros((M, N)).cuda()
+    if epi == 1:
+        res = RNG.standard_normal((M, N)).astype(np.float32)
+        out, ref = torch.tensor(res).cuda(), ref + res
+    elif epi == 2:
+        ref = oracle.gelu(ref)
+    assert _lib().revo_op_linear(FP32, epi, xd.data_ptr(), wd.data_ptr(), bd.data_ptr(), out.data_ptr(), M, N, K, None) == 0
+    torch.cuda.synchronize()
+    # FP32 accumulation over K terms, as in test_linear
+    tol = 2e-6 * math.sqrt(K) * np.abs(ref).max() + 1e-7
+    assert np.abs(out.double().cpu().numpy() - ref).max() <= tol
+
+
+# one shape per FP32 tile form (64 x 32, 64 x 64, 128 x 64, 128 x 128)
+@pytest.mark.parametrize("M,N,K", [(100, 64, 128), (2300, 576, 64), (3000, 512, 64), (6200, 1024, 64)])
+def test_linear_fp32_range(M, N, K):
+    """FP32 operands over the whole range: infinities, NaNs and the largest
+    values give what IEEE products and sums give, and rows of tiny and
+    subnormal values keep FP32 accuracy."""
+    x = RNG.standard_normal((M, K)).astype(np.float32)
+    w = RNG.standard_normal((N, K)).astype(np.float32)
+    w[np.abs(w) < 1e-3] = 1e-3                 # no zeros to meet an infinity
+    scale = np.ones((M, 1))
+    for i, e in enumerate((-20, -30, -37, -40)):   # 1e-20 .. subnormal rows
+        scale[10 + i] = 10.0 ** e
+    x[10:14] = (x[10:14].astype(np.float64) * scale[10:14]).astype(np.float32)
+    x[3, 5], x[4, 6], x[M - 1, K - 1] = np.inf, np.nan, -np.inf
+    x[5] = 0
+    x[5, 7] = 3.4e38                           # above the largest BF16
+    w[:, 7] *= 0.1
+    w[N - 2, 9] = np.inf
+    b = np.zeros(N, np.float32)
+    out = torch.zeros((M, N)).cuda()
+    xd, wd, bd = torch.tensor(x).cuda(), torch.tensor(w).cuda(), torch.tensor(b).cuda()
+    assert _lib().revo_op_linear(FP32, 0, xd.data_ptr(), wd.data_ptr(), bd.data_ptr(), out.data_ptr(), M, N, K, None) == 0
+    got = out.double().cpu().numpy()
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = np.where(np.isfinite(x), x, 0).astype(np.float64) @ np.where(np.isfinite(w), w, 0).astype(np.float64).T
+        # the infinities: the sign of their products, NaN where two disagree or meet a NaN
+        inf = np.zeros((M, N))
+        for m, k in ((3, 5), (M - 1, K - 1)):
+            inf[m] = x[m, k] * w[:, k]
+        inf[:, N - 2] += x[:, 9] * np.inf
+        inf[4] = np.nan
+    assert np.array_equal(np.isnan(got), np.isnan(inf))
+    assert np.array_equal(np.isinf(got), np.isinf(inf)) and np.array_equal(got[np.isinf(inf)], inf[np.isinf(inf)])
+    rows = np.isfinite(inf)
+    # per row: FP32 accumulation, a few float32 ulps of the row's largest sum,
+    # and the spacing of subnormal results
+    rowmax = np.abs(np.where(rows, ref, 0)).max(axis=1, keepdims=True)
+    err = np.where(rows, np.abs(np.where(rows, got, 0) - ref), 0)
+    assert np.all(err <= 2e-6 * math.sqrt(K) * rowmax + 2.0 ** -148)
+
+
 @pytest.mark.parametrize("prec", [FP32, BF16])
 @pytest.mark.parametrize("rows,D", [(1, 384), (1000, 384), (333, 192), (5, 24)])
 def test_layernorm(prec, rows, D):
