@@ -53,7 +53,7 @@ int revo_op_layernorm(int precision, const float *x, const float *g, const float
  * (c ^ ((c ^ (c >> 1)) & 4) * 3, a permutation inside each group of 16);
  * o [ntok][heads * 64].  ld >= ntok + 64, ld % 16 == 0, and rows ntok ..
  * ld-1 of q, k and columns ntok .. ld-1 of vt must hold finite values
- * (zeros). */
+ * (zeros).  Returns when the result is complete. */
 int revo_op_attention(int precision, const void *q, const void *k, const void *vt, void *o,
                       int heads, int ntok, int ld, void *stream);
 
@@ -69,20 +69,17 @@ int revo_op_attention(int precision, const void *q, const void *k, const void *v
  * in the order key t -> column (t & ~63) | ((t >> 2) & 1) << 5 |
  * ((t >> 5) & 1) << 4 | ((t >> 3) & 3) << 2 | (t & 3); rows / columns ntok ..
  * ld-1 zero.  o [ntok][heads 64] bfloat16.  ld % 64 == 0, ld >= ntok + 64.
- * Synchronous (descriptors are allocated and freed per call). */
+ * Returns when the result is complete. */
 int revo_op_attention_fp8(const void *q8, const void *k8, const void *vt8, void *o, int heads, int ntok, int ld,
                           const int *exps, void *stream);
 
-/* revo_op_attention for callers that cannot allocate device memory: code
- * under HIP graph capture, serving loops that must not call hipMalloc, and
- * harnesses that forbid it.  Same arguments, layouts and result as
- * revo_op_attention, but it allocates nothing, copies nothing from the host
- * and does not synchronise: the request descriptor and the q-tile work list
- * go to a fixed device workspace of 128.25 KiB (one per device, held until
- * the process ends), written by a kernel on `stream` before the attention
- * kernel.  ntok is at most 32767 * 128 = 4194176 tokens (REVO_E2BIG beyond).
- * Calls on one stream are ordered; calls that overlap on one device (other
- * streams or threads) share the workspace and race. */
+/* revo_op_attention without the wait: same arguments, layouts and result,
+ * but it only enqueues one kernel on `stream` (revo_op_attention returns when
+ * its result is complete).  Like revo_op_attention it allocates nothing and
+ * copies nothing from the host; the request is described in the launch's
+ * arguments, so calls share nothing and may overlap on any streams and
+ * threads, and the call can be captured in a graph.  ntok is at most 32767 *
+ * 128 = 4194176 tokens (REVO_E2BIG beyond). */
 int revo_op_attention_noalloc(int precision, const void *q, const void *k, const void *vt, void *o,
                               int heads, int ntok, int ld, void *stream);
 

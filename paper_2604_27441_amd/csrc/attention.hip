@@ -22,16 +22,13 @@
 // repeats its rows in a pass that raises the max lazily: a query keeps its
 // max until a block's scores exceed it by more than 8 (in log2 units), so
 // probabilities stay below 2^8 and the output rescale is skipped for almost
-// every block.  FP32 rows always use the lazy form.  Only the last key block
-// of a request checks key bounds.
-// K and V^T blocks of 64 keys are double-buffered in LDS.  BF16 blocks go
-// from HBM straight into LDS (buffer loads with an LDS destination, no
-// registers in between) with swizzled, unpadded rows; FP32 blocks pass
-// through registers.  Loads take scalar per-block offsets, and the block
-// loop runs two blocks per trip so both LDS buffers have fixed addresses.
+// every block.  FP32 rows (a kernel of their own, below) always use the lazy
+// form.  Only the last key block of a request checks key bounds.
+// K and V^T blocks of 64 keys are double-buffered in LDS and go there from HBM
+// directly (buffer loads with an LDS destination, no registers in between)
+// with swizzled, unpadded rows.  Loads take scalar per-block offsets, and the
+// block loop runs two blocks per trip so both LDS buffers have fixed addresses.
 #include <string.h>
-
-#include <mutex>
 
 #include "kernels.h"
 
@@ -67,16 +64,7 @@ __device__ __forceinline__ float xhalf_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <class T>
-struct AttnTile {
-  static constexpr int E = 16 / sizeof(T);   // elements per 16-byte chunk
-  // BF16 tiles arrive by DMA (whole 128-byte rows, unpadded, chunks
-  // swizzled); FP32 rows are padded by one chunk
-  static constexpr int PITCH = sizeof(T) == 2 ? 64 : 64 + E;  // LDS row pitch (elements)
-  static constexpr int CPR = 64 / E;         // 16-byte chunks per 64-element row
-  static constexpr int LC = KB * CPR / NT;   // chunks per thread per tile (FP32)
-  static constexpr int QCH = 32 / E;         // Q chunks per lane
-};
+constexpr int QCH = 4;  // 16-byte Q chunks per lane (BF16)
 
 // BF16 K and V^T tiles: row r (a key of K, a dimension of V^T) holds its
 // eight 16-byte chunks with chunk c at slot c ^ ((r >> 1) & 7), so the 16
@@ -84,52 +72,37 @@ struct AttnTile {
 __device__ __forceinline__ int swz(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3); }
 
 // One 64-key block for one wave: scores, online softmax, P V accumulation.
-template <class Op, bool MASK, bool FIRST, bool FAST>
-__device__ __forceinline__ void attn_block(const typename Op::T* __restrict__ kt, const typename Op::T* __restrict__ vt,
-                                           const uint4 (&qf)[AttnTile<typename Op::T>::QCH], f32x16 (&oacc)[2],
-                                           f32x16& negm, float& m_run, float& l_run, int lane, int kvalid) {
-  typedef typename Op::T T;
-  typedef AttnTile<T> A;
+template <bool MASK, bool FIRST, bool FAST>
+__device__ __forceinline__ void attn_block(const __bf16* __restrict__ kt, const __bf16* __restrict__ vt,
+                                           const uint4 (&qf)[QCH], f32x16 (&oacc)[2], f32x16& negm, float& m_run,
+                                           float& l_run, int lane, int kvalid) {
+  typedef OpBF16 Op;
   const int half = lane >> 5, l32 = lane & 31;
-  // BF16: after the first block the score products start from -m_run (all
-  // 16 registers of negm), so they come out already shifted by the max
-  constexpr bool SHIFTED = sizeof(T) == 2 && !FIRST;
+  // after the first block the score products start from -m_run (all 16
+  // registers of negm), so they come out already shifted by the max
 
   // S^T = K Q^T for two 32-key subtiles
   f32x16 sacc[2];
-  if constexpr (SHIFTED) {
+  if constexpr (!FIRST) {
     sacc[0] = negm;
     sacc[1] = negm;
   } else {
     sacc[0] = f32x16{};
     sacc[1] = f32x16{};
   }
-  if constexpr (sizeof(T) == 2) {
+  {
     // all eight K fragments in flight before the first product
-    uint4 kf[A::QCH][2];
+    uint4 kf[QCH][2];
 #pragma unroll
-    for (int kc = 0; kc < A::QCH; ++kc)
+    for (int kc = 0; kc < QCH; ++kc)
 #pragma unroll
       for (int st = 0; st < 2; ++st) kf[kc][st] = *reinterpret_cast<const uint4*>(kt + swz(st * 32 + l32, half * 4 + kc));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kc = 0; kc < A::QCH; ++kc)
+    for (int kc = 0; kc < QCH; ++kc)
 #pragma unroll
       for (int st = 0; st < 2; ++st)
         Op::mma(sacc[st], __builtin_bit_cast(bf16x8, kf[kc][st]), __builtin_bit_cast(bf16x8, qf[kc]));
-  }
-#pragma unroll
-  for (int kc = 0; kc < A::QCH; ++kc) {
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      if constexpr (sizeof(T) == 4) {
-        const uint4 kf = *reinterpret_cast<const uint4*>(kt + (st * 32 + l32) * A::PITCH + half * 32 + kc * A::E);
-        Op::mma(sacc[st], __uint_as_float(kf.x), __uint_as_float(qf[kc].x));
-        Op::mma(sacc[st], __uint_as_float(kf.y), __uint_as_float(qf[kc].y));
-        Op::mma(sacc[st], __uint_as_float(kf.z), __uint_as_float(qf[kc].z));
-        Op::mma(sacc[st], __uint_as_float(kf.w), __uint_as_float(qf[kc].w));
-      }
-    }
   }
   if constexpr (MASK) {
 #pragma unroll
@@ -139,10 +112,10 @@ __device__ __forceinline__ void attn_block(const typename Op::T* __restrict__ kt
         if (st * 32 + acc_row(i, lane) >= kvalid) sacc[st][i] = NEG_BIG;
   }
 
-  // FAST (BF16, after the first block): the max stays where the first block
-  // put it and no block max is taken; the caller checks the row sums after
-  // the last block instead
-  if constexpr (!(SHIFTED && FAST)) {
+  // FAST (after the first block): the max stays where the first block put it
+  // and no block max is taken; the caller checks the row sums after the last
+  // block instead
+  if constexpr (FIRST || !FAST) {
     // block max of this query
     float m0 = fmaxf(fmaxf(sacc[0][0], sacc[0][1]), sacc[0][2]);
     float m1 = fmaxf(fmaxf(sacc[1][0], sacc[1][1]), sacc[1][2]);
@@ -156,15 +129,13 @@ __device__ __forceinline__ void attn_block(const typename Op::T* __restrict__ kt
     if constexpr (FIRST) {
       // nothing accumulated yet: take this block's max as it is
       m_run = mloc;
-      if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) negm[i] = -mloc;
+      for (int i = 0; i < 16; ++i) negm[i] = -mloc;
 #pragma unroll
-        for (int st = 0; st < 2; ++st)
+      for (int st = 0; st < 2; ++st)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) sacc[st][i] -= mloc;
-      }
-    } else if constexpr (SHIFTED) {
+        for (int i = 0; i < 16; ++i) sacc[st][i] -= mloc;
+    } else {
       // mloc is relative to m_run here
       const bool grow = mloc > LAZY;
       if (__any(grow)) {
@@ -184,211 +155,153 @@ __device__ __forceinline__ void attn_block(const typename Op::T* __restrict__ kt
         // it become unconditional work with a selected factor
         asm volatile("" : "+v"(oacc[0]), "+v"(oacc[1]), "+v"(sacc[0]), "+v"(sacc[1]), "+v"(negm));
       }
-    } else {
-      const bool grow = mloc > m_run + LAZY;
-      if (__any(grow)) {
-        const float m_new = grow ? mloc : m_run;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        m_run = m_new;
-        l_run *= alpha;
-        oacc[0] *= alpha;
-        oacc[1] *= alpha;
-        asm volatile("" : "+v"(oacc[0]), "+v"(oacc[1]));
-      }
     }
   }
 
   // O^T += V^T P^T, contraction over the block's keys
-  if constexpr (sizeof(T) == 2) {
-    // row sum from the bf16-rounded probabilities that also feed the MFMA
-    const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
-    float ls0 = l_run, ls1 = 0.0f;
+  // row sum from the bf16-rounded probabilities that also feed the MFMA
+  const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+  float ls0 = l_run, ls1 = 0.0f;
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
+  for (int st = 0; st < 2; ++st) {
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        // registers 8g..8g+7 hold keys st*32 + g*16 + {half*4 + 0..3, 8 + half*4 + 0..3};
-        // V^T rows hold keys with bits 2 and 3 swapped, so those keys are the
-        // 8 contiguous elements at st*32 + g*16 + half*8
-        bf16x8 pf;
+    for (int g = 0; g < 2; ++g) {
+      // registers 8g..8g+7 hold keys st*32 + g*16 + {half*4 + 0..3, 8 + half*4 + 0..3};
+      // V^T rows hold keys with bits 2 and 3 swapped, so those keys are the
+      // 8 contiguous elements at st*32 + g*16 + half*8
+      bf16x8 pf;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pf[e] = (__bf16)__builtin_amdgcn_exp2f(sacc[st][8 * g + e]);
-        ls0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[0], pf[1]}, one, ls0, false);
-        ls1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[2], pf[3]}, one, ls1, false);
-        ls0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[4], pf[5]}, one, ls0, false);
-        ls1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[6], pf[7]}, one, ls1, false);
-        const int pos = st * 32 + g * 16 + half * 8;
+      for (int e = 0; e < 8; ++e) pf[e] = (__bf16)__builtin_amdgcn_exp2f(sacc[st][8 * g + e]);
+      ls0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[0], pf[1]}, one, ls0, false);
+      ls1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[2], pf[3]}, one, ls1, false);
+      ls0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[4], pf[5]}, one, ls0, false);
+      ls1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[6], pf[7]}, one, ls1, false);
+      const int pos = st * 32 + g * 16 + half * 8;
 #pragma unroll
-        for (int ds = 0; ds < 2; ++ds) {
-          const uint4 vv = *reinterpret_cast<const uint4*>(vt + swz(ds * 32 + l32, pos >> 3));
-          Op::mma(oacc[ds], __builtin_bit_cast(bf16x8, vv), pf);
-        }
-      }
-    }
-    l_run = ls0 + ls1;
-  } else {
-    float ls0 = 0.0f, ls1 = 0.0f;
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        sacc[st][i] = __builtin_amdgcn_exp2f(sacc[st][i] - m_run);
-        sacc[st][i + 1] = __builtin_amdgcn_exp2f(sacc[st][i + 1] - m_run);
-        ls0 += sacc[st][i];
-        ls1 += sacc[st][i + 1];
-      }
-    }
-    l_run += ls0 + ls1;
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        // registers 4g..4g+3 hold keys st*32 + g*8 + half*4 + 0..3
-        const int key = st * 32 + g * 8 + half * 4;
-#pragma unroll
-        for (int ds = 0; ds < 2; ++ds) {
-          const uint4 vv = *reinterpret_cast<const uint4*>(vt + (ds * 32 + l32) * A::PITCH + key);
-          Op::mma(oacc[ds], __uint_as_float(vv.x), sacc[st][4 * g + 0]);
-          Op::mma(oacc[ds], __uint_as_float(vv.y), sacc[st][4 * g + 1]);
-          Op::mma(oacc[ds], __uint_as_float(vv.z), sacc[st][4 * g + 2]);
-          Op::mma(oacc[ds], __uint_as_float(vv.w), sacc[st][4 * g + 3]);
-        }
+      for (int ds = 0; ds < 2; ++ds) {
+        const uint4 vv = *reinterpret_cast<const uint4*>(vt + swz(ds * 32 + l32, pos >> 3));
+        Op::mma(oacc[ds], __builtin_bit_cast(bf16x8, vv), pf);
       }
     }
   }
+  l_run = ls0 + ls1;
 }
 
-template <class Op>
-__global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_kernel(const AttnArgs a) {
-  typedef typename Op::T T;
-  typedef AttnTile<T> A;
-  // two K stages [key][dim], two V^T stages [dim][key], then a flag.  One
-  // LDS object only: with a second one the compiler attaches alias scopes to
-  // the stage loads and then waits for every prefetch before reading.
-  __shared__ __attribute__((aligned(16))) T kv[4 * KB * A::PITCH + 16 / sizeof(T)];
-  T(*ks)[KB * A::PITCH] = reinterpret_cast<T(*)[KB * A::PITCH]>(kv);
-  T(*vs)[KB * A::PITCH] = ks + 2;
-  int& redo = *reinterpret_cast<int*>(kv + 4 * KB * A::PITCH);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5;
-  // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
-  // L2).  Remap so that XCD x runs a contiguous range of (head, q-tile) work:
-  // the q-tiles of one request and head then share its K/V in one L2.
+// What a workgroup works on: head hd, queries q0 .. of the request of N tokens
+// at row base (work entries: see AttnArgs).
+struct AttnItem {
+  int hd, N, base, q0, tile;
+};
+// Workgroups are dispatched round-robin over the 8 XCDs (each with its own
+// L2).  Remap so that XCD x runs a contiguous range of (head, q-tile) work:
+// the q-tiles of one request and head then share its K/V in one L2.  False
+// past the live work (grid sized for a capacity).
+__device__ __forceinline__ bool attn_item(const AttnArgs& a, Prec p, AttnItem& it) {
   const int nwork = a.dyn_nwork ? *a.dyn_nwork : a.nwork;
   const int G = nwork * a.heads;
   const int L = blockIdx.x;
-  if (L >= G) return;  // grid sized for a capacity
+  if (L >= G) return false;
   const int xcd = L & 7, per = G >> 3, rem = G & 7;
   const int Lr = xcd * per + (xcd < rem ? xcd : rem) + (L >> 3);
-  const int hd = Lr / nwork;
-  const int w = a.work[Lr - hd * nwork];
-  const int r = w >> 16, qt = w & (ATTN_TARGET_TILE - 1);
-  const ReqDesc& d = a.reqs[r];
-  const int N = d.J * d.P;
-  const int base = d.tok_off;
+  it.hd = Lr / nwork;
+  const int i = Lr - it.hd * nwork;
+  if (!a.work) {
+    // one request of one_n tokens, tiles in order
+    it.N = a.one_n;
+    it.base = 0;
+    it.tile = a.tile ? a.tile : attn_tile(p, it.N);
+    it.q0 = i * it.tile;
+    return true;
+  }
+  const int w = a.work[i];
+  const ReqDesc& d = a.reqs[w >> 16];
+  it.N = d.J * d.P;
+  it.base = d.tok_off;
   // target-tubelet tiles (the last block, whose other queries feed nothing)
-  const int q0 = (w & ATTN_TARGET_TILE) ? (d.J - 1) * d.P : 0;
-  const int q_local = q0 + qt * QT + wave * 32 + (lane & 31);
+  it.tile = a.tile ? a.tile : attn_tile(p, it.N);
+  it.q0 = ((w & ATTN_TARGET_TILE) ? (d.J - 1) * d.P : 0) + (w & (ATTN_TARGET_TILE - 1)) * it.tile;
+  return true;
+}
+
+__global__ __launch_bounds__(NT, 3) void attn_kernel(const AttnArgs a) {
+  // two K stages [key][dim], two V^T stages [dim][key], then a flag.  One
+  // LDS object only: with a second one the compiler attaches alias scopes to
+  // the stage loads and then waits for every prefetch before reading.
+  __shared__ __attribute__((aligned(16))) __bf16 kv[4 * KB * 64 + 8];
+  __bf16(*ks)[KB * 64] = reinterpret_cast<__bf16(*)[KB * 64]>(kv);
+  __bf16(*vs)[KB * 64] = ks + 2;
+  int& redo = *reinterpret_cast<int*>(kv + 4 * KB * 64);
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5;
+  AttnItem it;
+  if (!attn_item(a, P_BF16, it)) return;
+  const int hd = it.hd, N = it.N, base = it.base, q0 = it.q0;
+  const int q_local = q0 + wave * 32 + (lane & 31);
   const int q = base + q_local;
 
-  const T* __restrict__ Kg = (const T*)a.k + ((size_t)hd * a.ldqk + base) * 64;
-  const T* __restrict__ Vg = (const T*)a.vt + (size_t)hd * 64 * a.ldv + base;
+  const __bf16* __restrict__ Kg = (const __bf16*)a.k + ((size_t)hd * a.ldqk + base) * 64;
+  const __bf16* __restrict__ Vg = (const __bf16*)a.vt + (size_t)hd * 64 * a.ldv + base;
 
   // Q^T fragment: this lane's query, dims [half*32, half*32 + 32); queries
   // past the request (ragged last tile) load row `base` and are never stored
-  uint4 qf[A::QCH];
+  uint4 qf[QCH];
   {
-    const T* qp = (const T*)a.q + ((size_t)hd * a.ldqk + (q_local < N ? q : base)) * 64 + half * 32;
+    const __bf16* qp = (const __bf16*)a.q + ((size_t)hd * a.ldqk + (q_local < N ? q : base)) * 64 + half * 32;
 #pragma unroll
-    for (int i = 0; i < A::QCH; ++i) qf[i] = reinterpret_cast<const uint4*>(qp)[i];
+    for (int i = 0; i < QCH; ++i) qf[i] = reinterpret_cast<const uint4*>(qp)[i];
   }
 
   const __amdgpu_buffer_rsrc_t krs =
-      __builtin_amdgcn_make_buffer_rsrc((void*)Kg, (short)0, (a.ldqk - base) * 64 * (int)sizeof(T), 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc((void*)Kg, (short)0, (a.ldqk - base) * 64 * 2, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrs =
-      __builtin_amdgcn_make_buffer_rsrc((void*)Vg, (short)0, (64 * a.ldv - base) * (int)sizeof(T), 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc((void*)Vg, (short)0, (64 * a.ldv - base) * 2, 0x00020000);
   // Stage loads for key block kb_ into LDS buffer buf_: FETCH starts them,
-  // LAND completes them (the caller then synchronises the workgroup).
-  //  BF16: buffer loads straight into LDS.  Wave w fills rows 16w .. 16w+15
-  //  of the K and V^T tiles, 8 rows (1 KB, 16 bytes per lane) per load; lane
-  //  L takes row 16w + 8j + L / 8 and the chunk whose swizzled slot is L % 8.
-  //  V^T arrives with bits 2 and 3 of the key index already swapped within
-  //  each group of 16 keys (the QKV epilogue writes it so; requests start on
-  //  16-key boundaries), so a lane's eight probabilities meet one 16-byte read.
-  //  FP32: 16-byte loads into registers, then LDS stores.
-  constexpr int R = NT / A::CPR;
-  const int c_row = tid / A::CPR;
-  const int c_col = (tid % A::CPR) * A::E;
+  // LAND completes them (the caller then synchronises the workgroup).  Wave w
+  // fills rows 16w .. 16w+15 of the K and V^T tiles, 8 rows (1 KB, 16 bytes per
+  // lane) per load; lane L takes row 16w + 8j + L / 8 and the chunk whose
+  // swizzled slot is L % 8.  V^T arrives with bits 2 and 3 of the key index
+  // already swapped within each group of 16 keys (the QKV epilogue writes it
+  // so; requests start on 16-key boundaries), so a lane's eight probabilities
+  // meet one 16-byte read.
   int kvo[2], vvo[2];
-  if constexpr (sizeof(T) == 2) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int rr = wave * 16 + 8 * j + (lane >> 3);
-      const int cc = (lane & 7) ^ ((rr >> 1) & 7);
-      kvo[j] = (rr * 64 + cc * 8) * (int)sizeof(T);
-      vvo[j] = (rr * a.ldv + cc * 8) * (int)sizeof(T);
-    }
-  } else {
-    kvo[0] = (c_row * 64 + c_col) * (int)sizeof(T);
-    vvo[0] = (c_row * a.ldv + c_col) * (int)sizeof(T);
-  }
-  uint4 kr0, kr1, kr2, kr3, vr0, vr1, vr2, vr3;
-#define REVO_ATTN_LOAD1(kb_, i_, kr_, vr_)                                                                       \
-  {                                                                                                              \
-    auto k_ = __builtin_amdgcn_raw_buffer_load_b128(krs, kvo[0], ((kb_) + (i_) * R) * 64 * (int)sizeof(T), 0);  \
-    auto v_ = __builtin_amdgcn_raw_buffer_load_b128(vrs, vvo[0], ((i_) * R * a.ldv + (kb_)) * (int)sizeof(T), 0); \
-    kr_ = make_uint4(k_[0], k_[1], k_[2], k_[3]);                                                                \
-    vr_ = make_uint4(v_[0], v_[1], v_[2], v_[3]);                                                                \
-  }
-#define REVO_ATTN_STORE1(buf_, i_, kr_, vr_)                                                          \
-  {                                                                                                   \
-    *reinterpret_cast<uint4*>(&ks[buf_][(c_row + (i_) * R) * A::PITCH + c_col]) = kr_;                \
-    *reinterpret_cast<uint4*>(&vs[buf_][(c_row + (i_) * R) * A::PITCH + c_col]) = vr_;                \
+  for (int j = 0; j < 2; ++j) {
+    const int rr = wave * 16 + 8 * j + (lane >> 3);
+    const int cc = (lane & 7) ^ ((rr >> 1) & 7);
+    kvo[j] = (rr * 64 + cc * 8) * 2;
+    vvo[j] = (rr * a.ldv + cc * 8) * 2;
   }
 #define REVO_ATTN_DMA(rs_, lds_, vo_, so_)                                                            \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_, (__attribute__((address_space(3))) void*)(lds_), 16, \
                                            vo_, so_, 0, 0)
-#define REVO_ATTN_FETCH(kb_, buf_)                                                                    \
-  if constexpr (sizeof(T) == 2) {                                                                     \
-    REVO_ATTN_DMA(krs, &ks[buf_][(wave * 16) * 64], kvo[0], (kb_) * 64 * (int)sizeof(T));             \
-    REVO_ATTN_DMA(krs, &ks[buf_][(wave * 16 + 8) * 64], kvo[1], (kb_) * 64 * (int)sizeof(T));         \
-    REVO_ATTN_DMA(vrs, &vs[buf_][(wave * 16) * 64], vvo[0], (kb_) * (int)sizeof(T));                  \
-    REVO_ATTN_DMA(vrs, &vs[buf_][(wave * 16 + 8) * 64], vvo[1], (kb_) * (int)sizeof(T));              \
-  } else {                                                                                            \
-    REVO_ATTN_LOAD1(kb_, 0, kr0, vr0)                                                                 \
-    REVO_ATTN_LOAD1(kb_, 1, kr1, vr1)                                                                 \
-    REVO_ATTN_LOAD1(kb_, 2, kr2, vr2)                                                                 \
-    REVO_ATTN_LOAD1(kb_, 3, kr3, vr3)                                                                 \
+#define REVO_ATTN_FETCH(kb_, buf_)                                             \
+  {                                                                            \
+    REVO_ATTN_DMA(krs, &ks[buf_][(wave * 16) * 64], kvo[0], (kb_) * 64 * 2);   \
+    REVO_ATTN_DMA(krs, &ks[buf_][(wave * 16 + 8) * 64], kvo[1], (kb_) * 64 * 2); \
+    REVO_ATTN_DMA(vrs, &vs[buf_][(wave * 16) * 64], vvo[0], (kb_) * 2);        \
+    REVO_ATTN_DMA(vrs, &vs[buf_][(wave * 16 + 8) * 64], vvo[1], (kb_) * 2);    \
   }
-#define REVO_ATTN_LAND(buf_)                                                                          \
-  if constexpr (sizeof(T) == 2) {                                                                     \
-    __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0): this wave's loads are in LDS */                  \
-  } else {                                                                                            \
-    REVO_ATTN_STORE1(buf_, 0, kr0, vr0)                                                               \
-    REVO_ATTN_STORE1(buf_, 1, kr1, vr1)                                                               \
-    REVO_ATTN_STORE1(buf_, 2, kr2, vr2)                                                               \
-    REVO_ATTN_STORE1(buf_, 3, kr3, vr3)                                                               \
-  }
-  static_assert(sizeof(T) == 2 || A::LC == 4, "FP32: 4 chunks per thread");
+  // vmcnt(0): this wave's loads are in LDS
+#define REVO_ATTN_LAND() __builtin_amdgcn_s_waitcnt(0x0F70)
 
   f32x16 oacc[2];
   f32x16 negm;
   float m_run, l_run;
   const int nkb = (N + KB - 1) / KB;
   const int nfull = N / KB;
-  // One pass over the key blocks.  FAST passes (BF16) keep the first block's
-  // max for the whole row (see attn_block); SAFE passes update it lazily.
-  // Written out in the kernel body (not a called function) so that the
-  // compiler keeps seeing the two LDS stages as distinct and does not wait
-  // for the prefetch before reading the current stage.
-#define REVO_ATTN_STEP(b_, buf_, fast_)                                                               \
-  {                                                                                                   \
-    const int kn_ = (b_) + 1 < nkb ? ((b_) + 1) * KB : (b_) * KB;                                     \
-    REVO_ATTN_FETCH(kn_, buf_ ^ 1);                                                                   \
-    attn_block<Op, false, false, fast_>(ks[buf_], vs[buf_], qf, oacc, negm, m_run, l_run, lane, KB);  \
-    REVO_ATTN_LAND(buf_ ^ 1);                                                                         \
-    __syncthreads();                                                                                  \
+  // One pass over the key blocks.  FAST passes keep the first block's max for
+  // the whole row (see attn_block); SAFE passes update it lazily.  Written out
+  // in the kernel body (not a called function) so that the compiler keeps
+  // seeing the two LDS stages as distinct and does not wait for the prefetch
+  // before reading the current stage.
+#define REVO_ATTN_STEP(b_, buf_, fast_)                                                         \
+  {                                                                                             \
+    const int kn_ = (b_) + 1 < nkb ? ((b_) + 1) * KB : (b_) * KB;                               \
+    REVO_ATTN_FETCH(kn_, buf_ ^ 1);                                                             \
+    attn_block<false, false, fast_>(ks[buf_], vs[buf_], qf, oacc, negm, m_run, l_run, lane, KB); \
+    REVO_ATTN_LAND();                                                                           \
+    __syncthreads();                                                                            \
   }
 #define REVO_ATTN_PASS(fast_)                                                                             \
   {                                                                                                       \
@@ -397,17 +310,17 @@ __global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_
     m_run = 0.0f;                                                                                         \
     l_run = 0.0f;                                                                                         \
     REVO_ATTN_FETCH(0, 0);                                                                                \
-    REVO_ATTN_LAND(0);                                                                                    \
+    REVO_ATTN_LAND();                                                                                     \
     __syncthreads();                                                                                      \
     if (nfull == 0) {                                                                                     \
       /* a single, ragged block */                                                                        \
-      attn_block<Op, true, true, fast_>(ks[0], vs[0], qf, oacc, negm, m_run, l_run, lane, N);             \
+      attn_block<true, true, fast_>(ks[0], vs[0], qf, oacc, negm, m_run, l_run, lane, N);                 \
     } else {                                                                                              \
       /* the first block sets the max; the prefetch of the next block (or, at the end, a re-read of its   \
          own block into the idle buffer, which is then never read) overlaps it */                         \
       REVO_ATTN_FETCH(nkb > 1 ? KB : 0, 1);                                                               \
-      attn_block<Op, false, true, fast_>(ks[0], vs[0], qf, oacc, negm, m_run, l_run, lane, KB);           \
-      REVO_ATTN_LAND(1);                                                                                  \
+      attn_block<false, true, fast_>(ks[0], vs[0], qf, oacc, negm, m_run, l_run, lane, KB);               \
+      REVO_ATTN_LAND();                                                                                   \
       __syncthreads();                                                                                    \
       int b = 1;                                                                                          \
       for (; b + 1 < nfull; b += 2) {                                                                     \
@@ -416,27 +329,21 @@ __global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_
       }                                                                                                   \
       if (b < nfull) REVO_ATTN_STEP(b, 1, fast_)                                                          \
       if (nfull < nkb) /* ragged last block, already in LDS */                                            \
-        attn_block<Op, true, false, fast_>(ks[nfull & 1], vs[nfull & 1], qf, oacc, negm, m_run, l_run, lane, \
-                                           N - nfull * KB);                                               \
+        attn_block<true, false, fast_>(ks[nfull & 1], vs[nfull & 1], qf, oacc, negm, m_run, l_run, lane,  \
+                                       N - nfull * KB);                                                   \
     }                                                                                                     \
   }
-  if constexpr (sizeof(T) == 2) {
-    // A FAST pass is exact as long as no probability overflowed: every
-    // probability of a lane's keys is at most that lane's row sum, so row sums
-    // below 2^64 bound them all (and the output by 2^64 max|v|).  Otherwise
-    // (or on NaN) the whole workgroup repeats the row in a SAFE pass.
-    if (tid == 0) redo = 0;  // ordered before any write by the pass's first barrier
-    REVO_ATTN_PASS(true)
-    if (__any(!(l_run < 0x1p64f)) && lane == 0) redo = 1;
-    __syncthreads();
-    if (redo) REVO_ATTN_PASS(false)  // every wave is past its last block
-  } else {
-    REVO_ATTN_PASS(false)
-  }
+  // A FAST pass is exact as long as no probability overflowed: every
+  // probability of a lane's keys is at most that lane's row sum, so row sums
+  // below 2^64 bound them all (and the output by 2^64 max|v|).  Otherwise
+  // (or on NaN) the whole workgroup repeats the row in a SAFE pass.
+  if (tid == 0) redo = 0;  // ordered before any write by the pass's first barrier
+  REVO_ATTN_PASS(true)
+  if (__any(!(l_run < 0x1p64f)) && lane == 0) redo = 1;
+  __syncthreads();
+  if (redo) REVO_ATTN_PASS(false)  // every wave is past its last block
 #undef REVO_ATTN_PASS
 #undef REVO_ATTN_STEP
-#undef REVO_ATTN_LOAD1
-#undef REVO_ATTN_STORE1
 #undef REVO_ATTN_DMA
 #undef REVO_ATTN_FETCH
 #undef REVO_ATTN_LAND
@@ -446,8 +353,6 @@ __global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_
   // 16-byte chunks rather than one short piece per query row.
   const float l_tot = xhalf_sum(l_run);
   const int ql = wave * 32 + (lane & 31);  // this lane's query within the tile
-  if (sizeof(T) == 4 && a.lse && lane < 32 && q_local < N)
-    a.lse[(size_t)hd * a.ldqk + q] = m_run + log2f(l_tot);  // P = exp2(s - lse)
   uint8_t* st = reinterpret_cast<uint8_t*>(kv);
   __syncthreads();
   if (a.o_scale) {
@@ -465,14 +370,13 @@ __global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_
     __syncthreads();
     for (int i = tid; i < QT * 4; i += NT) {
       const int row = i >> 2, c = (i & 3) * 16;
-      const int qr = q0 + qt * QT + row;
+      const int qr = q0 + row;
       if (qr < N)
         *reinterpret_cast<uint4*>((uint8_t*)a.o + (size_t)(base + qr) * (a.heads * 64) + hd * 64 + c) =
             *reinterpret_cast<const uint4*>(st + row * RB + c);
     }
   } else {
-    constexpr int RB = 64 * (int)sizeof(T) + 16;
-    constexpr int EC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
+    constexpr int RB = 64 * 2 + 16;
     static_assert(QT * RB <= (int)sizeof(kv), "output tile fits the K and V stages");
     const float inv = 1.0f / l_tot;
 #pragma unroll
@@ -480,25 +384,340 @@ __global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int dim = ds * 32 + g * 8 + half * 4;
-        T* sp = reinterpret_cast<T*>(st + ql * RB) + dim;
-        if constexpr (sizeof(T) == 2) {
-          *reinterpret_cast<bf16x4*>(sp) =
-              bf16x4{(__bf16)(oacc[ds][4 * g] * inv), (__bf16)(oacc[ds][4 * g + 1] * inv),
-                     (__bf16)(oacc[ds][4 * g + 2] * inv), (__bf16)(oacc[ds][4 * g + 3] * inv)};
-        } else {
-          *reinterpret_cast<f32x4*>(sp) = f32x4{oacc[ds][4 * g] * inv, oacc[ds][4 * g + 1] * inv,
-                                                oacc[ds][4 * g + 2] * inv, oacc[ds][4 * g + 3] * inv};
-        }
+        *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(st + ql * RB) + dim) =
+            bf16x4{(__bf16)(oacc[ds][4 * g] * inv), (__bf16)(oacc[ds][4 * g + 1] * inv),
+                   (__bf16)(oacc[ds][4 * g + 2] * inv), (__bf16)(oacc[ds][4 * g + 3] * inv)};
       }
     __syncthreads();
-    for (int i = tid; i < QT * (64 / EC); i += NT) {
-      const int row = i / (64 / EC), c = (i - row * (64 / EC)) * EC;
-      const int qr = q0 + qt * QT + row;
+    for (int i = tid; i < QT * 8; i += NT) {
+      const int row = i >> 3, c = (i & 7) * 8;
+      const int qr = q0 + row;
       if (qr < N)
-        *reinterpret_cast<uint4*>((T*)a.o + (size_t)(base + qr) * (a.heads * 64) + hd * 64 + c) =
-            *reinterpret_cast<const uint4*>(st + row * RB + c * (int)sizeof(T));
+        *reinterpret_cast<uint4*>((__bf16*)a.o + (size_t)(base + qr) * (a.heads * 64) + hd * 64 + c) =
+            *reinterpret_cast<const uint4*>(st + row * RB + c * 2);
     }
   }
+}
+
+// ---- FP32 form ---------------------------------------------------------------
+//
+// Q, K, V and the probabilities are split exactly into three BF16 parts each
+// (common.h split3, scaled by 2^24 against subnormal parts) and every product
+// of two FP32 values is the six largest of the nine products of their parts,
+// accumulated in FP32 on the BF16 matrix cores: 6 products at 16 times the
+// rate of the FP32 MFMA.  KG groups of QW waves (32 queries each) take every
+// KG-th key block, each with its own running max, row sum and output, which
+// are merged through LDS at the end; so a tile of 32 QW queries keeps two
+// waves on every SIMD.  K and V^T blocks go through registers (fetched one
+// round ahead), are split once per workgroup and lie in LDS as one BF16 plane
+// per part.
+//
+// The scores come out times 2^48 and the probabilities times 2^24, both undone
+// for free (the shift by the max is a multiply-add; the output divides by a
+// row sum with the same factor).  A row whose result is not finite (an
+// infinity or NaN among its operands, or scores past 2^80) is computed again
+// by FP32 MFMAs (attn_f32_row_tile).
+
+// The rows of one wave (32 queries) with FP32 MFMAs on operands from global
+// memory: scores, lazy max, probabilities, as in attn_block.
+__device__ __forceinline__ void attn_f32_row_tile(const AttnArgs& a, int hd, int N, int base, int q, f32x16 (&oacc)[2],
+                                               float& m_run, float& l_run) {
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const float* qp = (const float*)a.q + ((size_t)hd * a.ldqk + q) * 64;
+  const float* kp = (const float*)a.k + ((size_t)hd * a.ldqk + base) * 64;
+  const float* vp = (const float*)a.vt + (size_t)hd * 64 * a.ldv + base;
+  oacc[0] = f32x16{};
+  oacc[1] = f32x16{};
+  m_run = 0.0f;
+  l_run = 0.0f;
+#pragma unroll 1
+  for (int kb = 0; kb < N; kb += 32) {
+    f32x16 s = {};
+    const int kr = kb + l32 < N ? kb + l32 : N - 1;  // rows past the request are masked below
+#pragma unroll 1
+    for (int d = 0; d < 64; d += 2) OpF32::mma(s, kp[(size_t)kr * 64 + d + half], qp[d + half]);
+    float mloc = NEG_BIG;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (kb + acc_row(i, lane) >= N) s[i] = NEG_BIG;
+      mloc = fmaxf(mloc, s[i]);
+    }
+    mloc = xhalf_max(mloc);
+    const bool grow = kb == 0 || mloc > m_run + LAZY;
+    const float m_new = grow ? mloc : m_run;
+    const float alpha = kb == 0 ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+    if (kb > 0 && grow) {
+      l_run *= alpha;
+    }
+    m_run = m_new;
+#pragma unroll
+    for (int ds = 0; ds < 2; ++ds)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[ds][i] = kb > 0 && grow ? oacc[ds][i] * alpha : oacc[ds][i];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = __builtin_amdgcn_exp2f(s[i] - m_run);
+      l_run += s[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int key = kb + acc_row(i, lane);
+      const int kc = key < N ? key : N - 1;
+      const float p = key < N ? s[i] : 0.0f;
+#pragma unroll
+      for (int ds = 0; ds < 2; ++ds) {
+        const float v = key < N ? vp[(size_t)(ds * 32 + l32) * a.ldv + kc] : 0.0f;
+        OpF32::mma(oacc[ds], v, p);
+      }
+    }
+  }
+}
+
+// byte of 16-byte chunk c of row r of a plane with rows of KB BF16 values
+template <int KBF>
+__device__ __forceinline__ int f32_plane(int r, int c) {
+  static_assert(KBF == 32 || KBF == 64, "rows of 64 or 128 bytes");
+  return KBF == 32 ? r * 64 + ((c ^ ((r >> 2) & 3)) << 4) : r * 128 + ((c ^ ((r >> 1) & 7)) << 4);
+}
+
+constexpr int F32_NT = 512;       // threads per workgroup
+constexpr int F32_LDS = 98304;    // K and V^T planes of one block per key group
+
+template <int QW, int KG, int KBF>
+__device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem& it, uint8_t* smem) {
+  static_assert(64 * QW * KG == F32_NT, "eight waves");
+  constexpr int GT = 64 * QW;               // threads of a key group
+  constexpr int KP = KBF * 128, VP = 64 * KBF * 2;  // bytes per K / V^T plane
+  constexpr int GB = 3 * (KP + VP);
+  static_assert(KG * GB <= F32_LDS, "LDS");
+  constexpr int LC = KBF * 16 / GT;         // 16-byte chunks per thread of K and of V^T
+  constexpr int NST = KBF / 32;             // 32-key subtiles per block
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, l32 = lane & 31;
+  const int kg = wave / QW, qw = wave % QW, gt = tid - kg * GT;
+  const int hd = it.hd, N = it.N, base = it.base, q0 = it.q0;
+  const int q_local = q0 + qw * 32 + l32;
+  const int q = base + (q_local < N ? q_local : 0);  // queries past the request are never stored
+  uint8_t* ks = smem + kg * GB;
+  uint8_t* vs = ks + 3 * KP;
+
+  const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const float*)a.k + ((size_t)hd * a.ldqk + base) * 64), (short)0, (a.ldqk - base) * 64 * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const float*)a.vt + (size_t)hd * 64 * a.ldv + base), (short)0, (64 * a.ldv - base) * 4, 0x00020000);
+
+  // this lane's query: dims 8 c .. 8 c + 7, c = 2 s + half, for step s
+  bf16x8 qf[3][4];
+  {
+    const float4* qp = reinterpret_cast<const float4*>((const float*)a.q + ((size_t)hd * a.ldqk + q) * 64);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      uint2 lo[3], hi[3];
+      split3x4(qp[2 * (2 * s + half)], lo);
+      split3x4(qp[2 * (2 * s + half) + 1], hi);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) qf[j][s] = __builtin_bit_cast(bf16x8, make_uint4(lo[j].x, lo[j].y, hi[j].x, hi[j].y));
+    }
+  }
+  // stage chunks: K row c / 16, dims 4 (c % 16) ..; V^T row c / (KBF / 4), keys
+  // 4 (c % (KBF / 4)) .., stored with bits 2 and 3 of the key swapped (the
+  // order in which a lane's eight probabilities meet one 16-byte read)
+  float4 kr[LC], vr[LC];
+  auto fetch = [&](int kb) {
+#pragma unroll
+    for (int i = 0; i < LC; ++i) {
+      const int c = gt + i * GT;
+      kr[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(krs, c * 16, kb * 256, 0));
+      vr[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             vrs, ((c / (KBF / 4)) * a.ldv + (c % (KBF / 4)) * 4) * 4, kb * 4, 0));
+    }
+  };
+  auto land = [&]() {
+#pragma unroll
+    for (int i = 0; i < LC; ++i) {
+      const int c = gt + i * GT;
+      uint2 p[3];
+      split3x4(kr[i], p);
+      const int ko = f32_plane<64>(c / 16, (c % 16) >> 1) + (c & 1) * 8;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(ks + j * KP + ko) = p[j];
+      split3x4(vr[i], p);
+      const int u = c % (KBF / 4), up = (u & ~3) | ((u & 1) << 1) | ((u >> 1) & 1);
+      const int vo = f32_plane<KBF>(c / (KBF / 4), up >> 1) + (up & 1) * 8;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(vs + j * VP + vo) = p[j];
+    }
+  };
+  constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};  // smallest products first
+
+  f32x16 oacc[2];
+  oacc[0] = f32x16{};
+  oacc[1] = f32x16{};
+  float m_run = NEG_BIG, l_run = 0.0f;
+  const int nkb = (N + KBF - 1) / KBF, rounds = (nkb + KG - 1) / KG;
+  fetch(kg * KBF);
+  for (int t = 0; t < rounds; ++t) {
+    const int kb = (t * KG + kg) * KBF;
+    if (t > 0) __syncthreads();  // the previous block is consumed
+    land();
+    __syncthreads();
+    if (t + 1 < rounds) fetch(kb + KG * KBF);
+    if (kb >= N) continue;  // the last round of a group without a block (the barriers above still meet)
+    // S^T = K Q^T
+    f32x16 s[NST];
+#pragma unroll
+    for (int st = 0; st < NST; ++st) s[st] = f32x16{};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      bf16x8 kf[3][NST];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int st = 0; st < NST; ++st)
+          kf[j][st] = *reinterpret_cast<const bf16x8*>(ks + j * KP + f32_plane<64>(st * 32 + l32, 2 * c + half));
+#pragma unroll
+      for (int p = 0; p < 6; ++p)
+#pragma unroll
+        for (int st = 0; st < NST; ++st) OpBF16::mma(s[st], kf[PA[p]][st], qf[PB[p]][c]);
+    }
+    if (kb + KBF > N) {
+#pragma unroll
+      for (int st = 0; st < NST; ++st)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kb + st * 32 + acc_row(i, lane) >= N) s[st][i] = -INFINITY;
+    }
+    // lazy max (true scores are 2^-48 s)
+    float mx = s[0][0];
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[st][i]);
+    const float mloc = xhalf_max(mx) * 0x1p-48f;
+    const bool grow = mloc > m_run + LAZY;
+    if (__any(grow)) {
+      const float m_new = grow ? mloc : m_run;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
+      oacc[0] *= alpha;
+      oacc[1] *= alpha;
+      asm volatile("" : "+v"(oacc[0]), "+v"(oacc[1]));
+    }
+    // probabilities times 2^24, row sum, O^T += V^T P^T
+    const float sh = 24.0f - m_run;
+    float l0 = 0.0f, l1 = 0.0f;
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        uint32_t pw[3][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(s[st][8 * g + 2 * e], 0x1p-48f, sh));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(s[st][8 * g + 2 * e + 1], 0x1p-48f, sh));
+          l0 += p0;
+          l1 += p1;
+          split3(p0, p1, pw[0][e], pw[1][e], pw[2][e]);
+        }
+        bf16x8 pf[3], vf[3][2];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          pf[j] = __builtin_bit_cast(bf16x8, make_uint4(pw[j][0], pw[j][1], pw[j][2], pw[j][3]));
+#pragma unroll
+          for (int ds = 0; ds < 2; ++ds)
+            vf[j][ds] =
+                *reinterpret_cast<const bf16x8*>(vs + j * VP + f32_plane<KBF>(ds * 32 + l32, st * 4 + g * 2 + half));
+        }
+#pragma unroll
+        for (int p = 0; p < 6; ++p)
+#pragma unroll
+          for (int ds = 0; ds < 2; ++ds) OpBF16::mma(oacc[ds], vf[PA[p]][ds], pf[PB[p]]);
+      }
+    l_run += l0 + l1;
+  }
+  l_run = xhalf_sum(l_run);
+
+  // the other groups' maxima, sums and outputs into the first's, in order
+  // (O of group g, wave qw: 32 floats per lane at [i][lane])
+  float* red = reinterpret_cast<float*>(smem);
+  constexpr int RW = 34 * 64;
+  static_assert((KG - 1) * QW * RW * 4 <= F32_LDS, "merge buffer");
+  __syncthreads();  // every wave is past its last block
+  if (kg > 0) {
+    float* r = red + ((kg - 1) * QW + qw) * RW;
+    r[lane] = m_run;
+    r[64 + lane] = l_run;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      r[(2 + i) * 64 + lane] = oacc[0][i];
+      r[(18 + i) * 64 + lane] = oacc[1][i];
+    }
+  }
+  __syncthreads();
+  if (kg == 0) {
+#pragma unroll
+    for (int g = 0; g < KG - 1; ++g) {
+      const float* r = red + (g * QW + qw) * RW;
+      const float m2 = r[lane], l2 = r[64 + lane];
+      const float m_new = fmaxf(m_run, m2);
+      const float a1 = __builtin_amdgcn_exp2f(m_run - m_new), a2 = __builtin_amdgcn_exp2f(m2 - m_new);
+      m_run = m_new;
+      l_run = l_run * a1 + l2 * a2;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        oacc[0][i] = oacc[0][i] * a1 + r[(2 + i) * 64 + lane] * a2;
+        oacc[1][i] = oacc[1][i] * a1 + r[(18 + i) * 64 + lane] * a2;
+      }
+    }
+  }
+  __syncthreads();  // the merge buffer has been read: LDS takes the output tile
+  constexpr int RB = 64 * 4 + 16;
+  static_assert(32 * QW * RB <= F32_LDS, "output tile");
+  if (kg == 0) {
+    float t = l_run * 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t = fmaf(oacc[0][i], 0.0f, fmaf(oacc[1][i], 0.0f, t));
+    float inv;
+    if (__any(!(t == 0.0f) || !(l_run > 0.0f))) {
+      attn_f32_row_tile(a, hd, N, base, q, oacc, m_run, l_run);
+      l_run = xhalf_sum(l_run);
+      inv = 1.0f / l_run;
+    } else {
+      inv = 0x1p-24f / l_run;  // O holds 2^48, the row sum 2^24 times its value
+      l_run *= 0x1p-24f;
+    }
+    if (a.lse && lane < 32 && q_local < N)
+      a.lse[(size_t)hd * a.ldqk + q] = m_run + log2f(l_run);  // P = exp2(s - lse)
+#pragma unroll
+    for (int ds = 0; ds < 2; ++ds)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4*>(smem + (qw * 32 + l32) * RB + (ds * 32 + g * 8 + half * 4) * 4) =
+            f32x4{oacc[ds][4 * g] * inv, oacc[ds][4 * g + 1] * inv, oacc[ds][4 * g + 2] * inv, oacc[ds][4 * g + 3] * inv};
+  }
+  __syncthreads();
+  for (int i = tid; i < 32 * QW * 16; i += F32_NT) {
+    const int row = i >> 4, c = (i & 15) * 4;
+    const int qr = q0 + row;
+    if (qr < N)
+      *reinterpret_cast<uint4*>((float*)a.o + (size_t)(base + qr) * (a.heads * 64) + hd * 64 + c) =
+          *reinterpret_cast<const uint4*>(smem + row * RB + c * 4);
+  }
+}
+
+// One workgroup per work entry and head.  What bounds it at full load is the
+// matrix cores: 6 heads of 10800 tokens take 954 us, 188 TFLOP/s of FP32 work
+// or 1128 TFLOP/s of BF16 products (FP32 MFMAs: 1371 us); 6 heads of 3600
+// tokens, 174 workgroups on 256 CUs, 247 -> 148 us; 6 heads of 576 43.7 ->
+// 21.6 us.  Errors against 64 bits fall from 1.3e-6 to 9.2e-7 relative at 3600
+// tokens and from 2.1e-6 to 1.2e-6 at 10800.
+__global__ __launch_bounds__(F32_NT, 2) void attn_f32_kernel(const AttnArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[F32_LDS];
+  AttnItem it;
+  if (!attn_item(a, P_FP32, it)) return;
+  if (it.tile == 64) attn_f32_tile<2, 4, 32>(a, it, smem);
+  else attn_f32_tile<4, 2, 64>(a, it, smem);
 }
 
 // ---- FP8 form ----------------------------------------------------------------
@@ -518,6 +737,13 @@ __global__ __launch_bounds__(NT, sizeof(typename Op::T) == 2 ? 3 : 2) void attn_
 // 64-token boundaries), so a lane's probabilities are its 32 consecutive k.
 
 __device__ __forceinline__ int swz8(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
+
+// E8M0 exponents of an attn_fp8_kernel launch: a device array (the network's
+// calibration) or, for the one-request entry point, values in the launch
+struct Fp8Exps {
+  const int* dev;
+  uint8_t val[3 * ATTN_MAX_OP_HEADS];
+};
 
 __device__ __forceinline__ f32x16 mfma_fp8(const i32x8& a, const i32x8& b, const f32x16& c, int sa, int sb) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, sa, 0, sb);
@@ -607,30 +833,22 @@ __device__ __forceinline__ void fp8_block(const uint8_t* __restrict__ kt, const 
   lacc = mfma_fp8(ones, pf, lacc, 127, 127);
 }
 
-__global__ __launch_bounds__(NT, 3) void attn_fp8_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(NT, 3) void attn_fp8_kernel(const AttnArgs a, const Fp8Exps exps) {
   constexpr int TB = KB * 64;  // bytes per K or V^T tile
   __shared__ __attribute__((aligned(16))) uint8_t kv[4 * TB];
   uint8_t* ks = kv;
   uint8_t* vs = kv + 2 * TB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5;
-  const int nwork = a.dyn_nwork ? *a.dyn_nwork : a.nwork;
-  const int G = nwork * a.heads;
-  const int L = blockIdx.x;
-  if (L >= G) return;
-  const int xcd = L & 7, per = G >> 3, rem = G & 7;
-  const int Lr = xcd * per + (xcd < rem ? xcd : rem) + (L >> 3);
-  const int hd = Lr / nwork;
-  const int w = a.work[Lr - hd * nwork];
-  const int r = w >> 16, qt = w & (ATTN_TARGET_TILE - 1);
-  const ReqDesc& d = a.reqs[r];
-  const int N = d.J * d.P;
-  const int base = d.tok_off;
-  const int q0 = (w & ATTN_TARGET_TILE) ? (d.J - 1) * d.P : 0;
-  const int q_local = q0 + qt * QT + wave * 32 + (lane & 31);
+  AttnItem it;
+  if (!attn_item(a, P_FP8, it)) return;
+  const int hd = it.hd, N = it.N, base = it.base, q0 = it.q0;
+  const int q_local = q0 + wave * 32 + (lane & 31);
   const int q = base + q_local;
   // E8M0 scale operands (127 + e)
-  const int sq = a.qkv_exp[hd], sk = a.qkv_exp[a.heads + hd], sv = a.qkv_exp[2 * a.heads + hd];
+  const int sq = exps.dev ? exps.dev[hd] : exps.val[hd];
+  const int sk = exps.dev ? exps.dev[a.heads + hd] : exps.val[a.heads + hd];
+  const int sv = exps.dev ? exps.dev[2 * a.heads + hd] : exps.val[2 * a.heads + hd];
 
   const uint8_t* Kg = (const uint8_t*)a.k + ((size_t)hd * a.ldqk + base) * 64;
   const uint8_t* Vg = (const uint8_t*)a.vt + (size_t)hd * 64 * a.ldv + base;
@@ -720,7 +938,7 @@ __global__ __launch_bounds__(NT, 3) void attn_fp8_kernel(const AttnArgs a) {
     __syncthreads();
     for (int i = tid; i < QT * 4; i += NT) {
       const int row = i >> 2, c = (i & 3) * 16;
-      const int qr = q0 + qt * QT + row;
+      const int qr = q0 + row;
       if (qr < N)
         *reinterpret_cast<uint4*>((uint8_t*)a.o + (size_t)(base + qr) * (a.heads * 64) + hd * 64 + c) =
             *reinterpret_cast<const uint4*>(st + row * RB + c);
@@ -745,7 +963,7 @@ __global__ __launch_bounds__(NT, 3) void attn_fp8_kernel(const AttnArgs a) {
       __syncthreads();
       for (int i = tid; i < 64 * 8; i += NT) {
         const int row = i >> 3, c = (i & 7) * 8;
-        const int qr = q0 + qt * QT + pass * 64 + row;
+        const int qr = q0 + pass * 64 + row;
         if (qr < N)
           *reinterpret_cast<uint4*>((__bf16*)a.o + (size_t)(base + qr) * (a.heads * 64) + hd * 64 + c) =
               *reinterpret_cast<const uint4*>(st + row * RB + c * 2);
@@ -757,90 +975,35 @@ __global__ __launch_bounds__(NT, 3) void attn_fp8_kernel(const AttnArgs a) {
 
 }  // namespace
 
-int launch_attention(Prec prec, const AttnArgs& a, hipStream_t s) {
+int launch_attention(Prec prec, const AttnArgs& a, hipStream_t s, const uint8_t* exps) {
   if (a.nwork <= 0) return 0;
   dim3 grid(a.nwork * a.heads);
-  if (prec == P_FP8 && a.qkv_exp) attn_fp8_kernel<<<grid, NT, 0, s>>>(a);
-  else if (prec == P_BF16 || prec == P_FP8) attn_kernel<OpBF16><<<grid, NT, 0, s>>>(a);  // uncalibrated FP8 form: BF16
-  else if (prec == P_FP32 && !a.o_scale) attn_kernel<OpF32><<<grid, NT, 0, s>>>(a);
-  else return -95;
+  if (prec == P_FP8 && (a.qkv_exp || exps)) {
+    Fp8Exps e;
+    e.dev = a.qkv_exp;
+    if (!a.qkv_exp) {
+      if (a.heads > ATTN_MAX_OP_HEADS) return -22;
+      memcpy(e.val, exps, 3 * a.heads);
+    }
+    attn_fp8_kernel<<<grid, NT, 0, s>>>(a, e);
+  } else if (prec == P_BF16 || prec == P_FP8) {
+    attn_kernel<<<grid, NT, 0, s>>>(a);  // uncalibrated FP8 form: BF16
+  } else if (prec == P_FP32 && !a.o_scale) {
+    attn_f32_kernel<<<grid, F32_NT, 0, s>>>(a);
+  } else {
+    return -95;
+  }
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }
 
-// ---- Attention without allocation ------------------------------------------
-//
-// The one-request form of the attention kernel needs a request descriptor
-// and a q-tile work list in device memory.  This variant keeps both in a
-// file-scope device array (one copy per device, held until the process
-// ends): a small kernel on the caller's stream writes them, then the
-// attention kernel reads them.  Calls on one stream are ordered; calls that
-// overlap on one device (other streams, other threads) share the array and
-// race.
-
-namespace {
-
-constexpr size_t NOALLOC_DESC_BYTES = 256;
-static_assert(sizeof(ReqDesc) <= NOALLOC_DESC_BYTES, "request descriptor slot too small");
-constexpr size_t NOALLOC_BYTES = NOALLOC_DESC_BYTES + sizeof(int) * (ATTN_NOALLOC_MAX_TILES + 1);
-constexpr int NOALLOC_MAX_DEVICES = 64;
-
-std::mutex g_noalloc_mu;
-void* g_noalloc_ptr[NOALLOC_MAX_DEVICES] = {};
-
-// Descriptor of one request covering every token (one tubelet of ntok
-// tokens, no frames) and the work list 0 .. ntile-1; every value the
-// attention kernel reads is rewritten, so nothing needs clearing first.
-__global__ void attn_noalloc_setup_kernel(unsigned char* ws, int ntok, int ntile) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    ReqDesc* d = reinterpret_cast<ReqDesc*>(ws);
-    d->tok_off = 0; d->head_off = 0;
-    d->H = 1; d->W = ntok; d->gy = 1; d->gx = ntok; d->P = ntok;
-    d->J = 1; d->nframes = 1; d->pad_ = 0;
-    for (int f = 0; f < REVO_MAX_FRAMES; ++f) { d->tau[f] = 0.f; d->frames[f] = nullptr; }
-    d->mask = nullptr; d->pred = nullptr; d->out_i = nullptr; d->out_f = nullptr;
-  }
-  int* work = reinterpret_cast<int*>(ws + NOALLOC_DESC_BYTES);
-  if (i < ntile) work[i] = i;
-}
-
-}  // namespace
-
-static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
-
-namespace {
-
-// Device address of this device's copy of the array, looked up once per
-// device (the array's name is not a device address in host code).
-int noalloc_workspace(unsigned char** out) {
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= NOALLOC_MAX_DEVICES) return -5;
-  std::lock_guard<std::mutex> lk(g_noalloc_mu);
-  if (!g_noalloc_ptr[dev]) {
-    void* p = nullptr;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return -5;
-    g_noalloc_ptr[dev] = p;
-  }
-  *out = static_cast<unsigned char*>(g_noalloc_ptr[dev]);
-  return 0;
-}
-
-}  // namespace
-
-int launch_attention_noalloc(Prec prec, const void* q, const void* k, const void* vt, void* o, int heads, int ntok,
-                             int ld, hipStream_t s) {
-  const int ntile = (ntok + 127) / 128;
-  if (ntok <= 0 || ntile > ATTN_NOALLOC_MAX_TILES) return -7;
-  unsigned char* ws = nullptr;
-  if (int rc = noalloc_workspace(&ws)) return rc;
-  attn_noalloc_setup_kernel<<<(ntile + 255) / 256, 256, 0, s>>>(ws, ntok, ntile);
-  if (hipGetLastError() != hipSuccess) return -5;
+int launch_attention_one(Prec prec, const void* q, const void* k, const void* vt, void* o, int heads, int ntok, int ld,
+                         const uint8_t* exps, hipStream_t s) {
   AttnArgs a;
   memset(&a, 0, sizeof(a));
   a.q = q; a.k = k; a.vt = vt; a.o = o; a.heads = heads; a.ldqk = ld; a.ldv = ld;
-  a.reqs = reinterpret_cast<const ReqDesc*>(ws); a.nreq = 1;
-  a.work = reinterpret_cast<const int*>(ws + NOALLOC_DESC_BYTES); a.nwork = ntile;
-  return launch_attention(prec, a, s);
+  a.one_n = ntok;
+  a.nwork = cdiv(ntok, attn_tile(prec, ntok));
+  return launch_attention(prec, a, s, exps);
 }
 
 }  // namespace revo

@@ -89,16 +89,15 @@ __device__ inline float to_float(__bf16 x) { return (float)x; }
 // (l & 31) and, in register i, row (i / 4) * 8 + (l / 32) * 4 + (i % 4).
 __device__ inline int acc_row(int i, int lane) { return (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3); }
 
-// Exact split of four floats times 2^24 into three BF16 parts each, 2^24 x =
-// p0 + p1 + p2 with every part the nearest BF16 to what is left (|p1| <= 2^-9,
-// |p2| <= 2^-18 of |2^24 x|; 24 bits of mantissa are 8 + 8 + 8): part j of the
-// four in p[j].  The scale keeps every part out of the subnormal range.
+// split3: exact split of two floats into three BF16 parts each, x = p0 + p1 +
+// p2 with every part the nearest BF16 to what is left (|p1| <= 2^-9 |x|, |p2|
+// <= 2^-18 |x|; 24 bits of mantissa are 8 + 8 + 8); part j of the two in pj.
+// split3x4: four floats times 2^24, part j of the four in p[j].  The scale
+// keeps every part out of the subnormal range, which the BF16 MFMA flushes.
 __device__ inline uint32_t bf16_pack(float a, float b) {
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
-__device__ inline void split3x2(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
-  a *= 0x1p24f;
-  b *= 0x1p24f;
+__device__ inline void split3(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
   p0 = bf16_pack(a, b);
   a -= __uint_as_float(p0 << 16);
   b -= __uint_as_float(p0 & 0xFFFF0000u);
@@ -108,8 +107,8 @@ __device__ inline void split3x2(float a, float b, uint32_t& p0, uint32_t& p1, ui
   p2 = bf16_pack(a, b);
 }
 __device__ inline void split3x4(const float4& v, uint2 (&p)[3]) {
-  split3x2(v.x, v.y, p[0].x, p[1].x, p[2].x);
-  split3x2(v.z, v.w, p[0].y, p[1].y, p[2].y);
+  split3(v.x * 0x1p24f, v.y * 0x1p24f, p[0].x, p[1].x, p[2].x);
+  split3(v.z * 0x1p24f, v.w * 0x1p24f, p[0].y, p[1].y, p[2].y);
 }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }

@@ -72,6 +72,16 @@ struct GemmArgs {
 };
 
 constexpr int ATTN_TARGET_TILE = 0x8000;
+constexpr int ATTN_MAX_OP_HEADS = 64;  // heads of a launch whose E8M0 exponents travel in its arguments
+
+// Queries per work entry of a request of N tokens.  FP32 requests of at most
+// 1024 tokens take 64-query tiles whose waves split the keys four ways: 6
+// heads of 576 tokens are then 54 workgroups of 5 rounds (21.6 us; 30
+// workgroups of 5 twice as long rounds 28.8 us), 1024 tokens 33 us.  The rule
+// looks at the request alone, so that its result is the same in every batch;
+// a launch that fills the GPU whatever its tiles (AttnArgs::tile) does better
+// with 128 (48 heads of 576 tokens 47 against 35 us).
+__host__ __device__ inline int attn_tile(Prec p, int N) { return p == P_FP32 && N <= 1024 ? 64 : 128; }
 
 struct AttnArgs {
   const void* q;     // [heads][ldqk rows][64], pre-scaled by log2(e)/sqrt(64)
@@ -80,9 +90,13 @@ struct AttnArgs {
   void* o;           // [M][heads * 64]
   int heads, ldqk, ldv;
   const ReqDesc* reqs; int nreq;
-  // per workgroup: (request << 16) | q-tile, with ATTN_TARGET_TILE set for a
-  // q-tile of the request's target tubelet only (queries from (J-1)*P on)
+  // per workgroup: (request << 16) | q-tile (of attn_tile queries), with
+  // ATTN_TARGET_TILE set for a q-tile of the request's target tubelet only
+  // (queries from (J-1)*P on).  Null: one request of one_n tokens from row 0
+  // on, its tiles in order (reqs is not read).
   const int* work;
+  int one_n;
+  int tile;          // queries per work entry where not attn_tile's (0: attn_tile's)
   int nwork;         // sizes the grid; the live count is *dyn_nwork when set
   const int* dyn_nwork;  // nullable
   const int* dyn_nreq;   // nullable
@@ -105,14 +119,15 @@ int launch_gemm(Prec prec, int epi, int xmode, const GemmArgs& a, hipStream_t s)
 // channels, dyn_m / dyn_nreq) written to out as a dense [M][K] operand
 // (float for P_FP32, bfloat16 otherwise).
 int launch_tubelet_pack(Prec prec, const GemmArgs& a, void* out, hipStream_t s);
-int launch_attention(Prec prec, const AttnArgs& a, hipStream_t s);
-// Attention of one request of ntok tokens whose descriptor and q-tile work
-// list live in a fixed per-device workspace instead of allocated memory:
-// no allocation, no host copy, no synchronisation.  At most
-// ATTN_NOALLOC_MAX_TILES q-tiles of 128 tokens (-7 beyond).
-constexpr int ATTN_NOALLOC_MAX_TILES = ATTN_TARGET_TILE - 1;
-int launch_attention_noalloc(Prec prec, const void* q, const void* k, const void* vt, void* o, int heads, int ntok,
-                             int ld, hipStream_t s);
+// exps: the E8M0 exponents [3][heads] of an FP8 launch without qkv_exp (host)
+int launch_attention(Prec prec, const AttnArgs& a, hipStream_t s, const uint8_t* exps = nullptr);
+// Attention of one request of ntok tokens, described in the launch's
+// arguments: no allocation, no host copy, no synchronisation, nothing shared
+// between calls.
+int launch_attention_one(Prec prec, const void* q, const void* k, const void* vt, void* o, int heads, int ntok, int ld,
+                         const uint8_t* exps, hipStream_t s);
+// q-tiles of 128 tokens of the largest request the entry points take
+constexpr int ATTN_MAX_TILES = ATTN_TARGET_TILE - 1;
 // y = LN(x) * g + b over rows of length D.  With reqs set, output row i is
 // the target-tubelet token (i - head_off) of the request owning compact row i.
 int launch_layernorm(Prec out_prec, const float* x, const float* g, const float* b,

@@ -176,6 +176,10 @@ struct ProfScope {
 
 int request_tokens(int H, int W, int J) { return J * cdiv(H, REVO_PATCH) * cdiv(W, REVO_PATCH); }
 
+namespace {
+int min_attn_tile(Prec p) { return attn_tile(p, 1); }
+}  // namespace
+
 size_t workspace_bytes(const ModelW& m, int cap, int max_req) {
   const size_t e = esize(m.prec);
   const size_t ld = (size_t)cap + 64;
@@ -189,13 +193,13 @@ size_t workspace_bytes(const ModelW& m, int cap, int max_req) {
   b += (size_t)cap * 4 * De * e;         // hid
   b += (size_t)cap * m.Dd * 4;           // z
   b += (size_t)cap * m.Dd * e;           // ahead (target rows <= cap)
-  b += (size_t)max_req * sizeof(ReqDesc) + 2 * (size_t)(cap / 128 + max_req + 1) * 4 + HDR_N * 4;
+  b += (size_t)max_req * sizeof(ReqDesc) + 2 * (size_t)(cap / min_attn_tile(m.prec) + max_req + 1) * 4 + HDR_N * 4;
   return b + 16 * 256;
 }
 
 int workspace_alloc(Workspace& w, const ModelW& m, int cap, int max_req, hipStream_t s) {
   w.cap = cap; w.head_cap = cap; w.ld = cap + 64; w.max_req = max_req; w.prec = m.prec;
-  w.max_work = cap / 128 + max_req + 1;
+  w.max_work = cap / min_attn_tile(m.prec) + max_req + 1;
   const size_t e = esize(m.prec);
   const size_t De = m.De;
   auto get = [&](void** p, size_t bytes) -> int {
@@ -412,11 +416,12 @@ int forward(const ModelW& m, Workspace& w, int slot, int nrec, int nall, int com
     d.tok_off = M;
     d.head_off = Mh;
     const int N = d.J * d.P;
-    for (int qt = 0; qt * 128 < N; ++qt) {
+    const int tile = attn_tile(m.prec, N);
+    for (int qt = 0; qt * tile < N; ++qt) {
       if (nwork >= w.max_work) return -22;
       work[nwork++] = (r << 16) | qt;
     }
-    for (int qt = 0; qt * 128 < d.P; ++qt) {
+    for (int qt = 0; qt * tile < d.P; ++qt) {
       if (nwork_last >= w.max_work) return -22;
       work_last[nwork_last++] = (r << 16) | ATTN_TARGET_TILE | qt;
     }
@@ -444,7 +449,7 @@ int forward(const ModelW& m, Workspace& w, int slot, int nrec, int nall, int com
   while (b + 1 < WS_BUCKETS && (w.cap >> (WS_BUCKETS - 1 - b)) < M) ++b;
   const int capM = w.cap >> (WS_BUCKETS - 1 - b);
   if (!w.graph[b]) {
-    const int capW = capM / 128 + w.max_req;
+    const int capW = capM / min_attn_tile(m.prec) + w.max_req;
     const int capPix = 4096 * 4096;
     hipGraph_t g = nullptr;
     REVO_HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));

@@ -2,9 +2,6 @@
 // kernels the forward pass uses, for per-kernel checks.
 #include <string.h>
 
-#include <mutex>
-#include <vector>
-
 #include "../../include/revo.h"
 #include "../../include/revo_ops.h"
 #include "kernels.h"
@@ -77,74 +74,25 @@ int revo_op_attention(int precision, const void* q, const void* k, const void* v
   if (!prec_of(precision, &p)) return REVO_ENOTSUP;
   if (heads <= 0 || ntok <= 0 || ld < ntok + 64 || !q || !k || !vt || !o) return REVO_EINVAL;
   if (ld % 16) return REVO_EINVAL;  // 16-byte aligned vt rows, whole key groups of 16
-  const int ntile = (ntok + 127) / 128;
-  if (ntile >= ATTN_TARGET_TILE) return REVO_EINVAL;
+  if ((ntok + 127) / 128 > ATTN_MAX_TILES) return REVO_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  // one request covering all tokens; descriptor and work list in device memory
-  ReqDesc h;
-  memset(&h, 0, sizeof(h));
-  h.J = 1; h.P = ntok; h.gy = 1; h.gx = ntok; h.H = 1; h.W = ntok; h.nframes = 1;
-  ReqDesc* d = nullptr;
-  int* work = nullptr;
-  if (hipMalloc(&d, sizeof(ReqDesc)) != hipSuccess) return REVO_ENOMEM;
-  if (hipMalloc(&work, ntile * sizeof(int)) != hipSuccess) { (void)hipFree(d); return REVO_ENOMEM; }
-  int* hw = new int[ntile];
-  for (int i = 0; i < ntile; ++i) hw[i] = i;
-  int rc = 0;
-  if (hipMemcpy(d, &h, sizeof(h), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(work, hw, ntile * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
-    rc = REVO_EDEVICE;
-  delete[] hw;
-  if (!rc) {
-    AttnArgs a;
-    memset(&a, 0, sizeof(a));
-    a.q = q; a.k = k; a.vt = vt; a.o = o; a.heads = heads; a.ldqk = ld; a.ldv = ld;
-    a.reqs = d; a.nreq = 1; a.work = work; a.nwork = ntile;
-    rc = launch_attention(p, a, s);
-    if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = REVO_EDEVICE;
-  }
-  (void)hipFree(d);
-  (void)hipFree(work);
+  int rc = launch_attention_one(p, q, k, vt, o, heads, ntok, ld, nullptr, s);
+  if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = REVO_EDEVICE;
   return rc;
 }
 
 int revo_op_attention_fp8(const void* q8, const void* k8, const void* vt8, void* o, int heads, int ntok, int ld,
                           const int* exps, void* stream) {
-  if (heads <= 0 || heads > 64 || ntok <= 0 || ld < ntok + 64 || !q8 || !k8 || !vt8 || !o || !exps) return REVO_EINVAL;
+  if (heads <= 0 || heads > ATTN_MAX_OP_HEADS || ntok <= 0 || ld < ntok + 64 || !q8 || !k8 || !vt8 || !o || !exps) return REVO_EINVAL;
   if (ld % 64) return REVO_EINVAL;  // whole 64-key groups of V^T, 16-byte aligned rows
   for (int i = 0; i < 3 * heads; ++i)
     if (exps[i] < -100 || exps[i] > 100) return REVO_EINVAL;
-  const int ntile = (ntok + 127) / 128;
-  if (ntile >= ATTN_TARGET_TILE) return REVO_EINVAL;
+  if ((ntok + 127) / 128 > ATTN_MAX_TILES) return REVO_EINVAL;
+  uint8_t he[3 * ATTN_MAX_OP_HEADS];
+  for (int i = 0; i < 3 * heads; ++i) he[i] = (uint8_t)(127 + exps[i]);
   hipStream_t s = (hipStream_t)stream;
-  ReqDesc h;
-  memset(&h, 0, sizeof(h));
-  h.J = 1; h.P = ntok; h.gy = 1; h.gx = ntok; h.H = 1; h.W = ntok; h.nframes = 1;
-  std::vector<int> hw(ntile);
-  for (int i = 0; i < ntile; ++i) hw[i] = i;
-  std::vector<int> he(3 * heads);
-  for (int i = 0; i < 3 * heads; ++i) he[i] = 127 + exps[i];
-  ReqDesc* d = nullptr;
-  int *work = nullptr, *de = nullptr;
-  int rc = 0;
-  if (hipMalloc(&d, sizeof(ReqDesc)) != hipSuccess || hipMalloc(&work, ntile * sizeof(int)) != hipSuccess ||
-      hipMalloc(&de, 3 * heads * sizeof(int)) != hipSuccess)
-    rc = REVO_ENOMEM;
-  if (!rc && (hipMemcpy(d, &h, sizeof(h), hipMemcpyHostToDevice) != hipSuccess ||
-              hipMemcpy(work, hw.data(), ntile * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-              hipMemcpy(de, he.data(), 3 * heads * sizeof(int), hipMemcpyHostToDevice) != hipSuccess))
-    rc = REVO_EDEVICE;
-  if (!rc) {
-    AttnArgs a;
-    memset(&a, 0, sizeof(a));
-    a.q = q8; a.k = k8; a.vt = vt8; a.o = o; a.heads = heads; a.ldqk = ld; a.ldv = ld;
-    a.reqs = d; a.nreq = 1; a.work = work; a.nwork = ntile; a.qkv_exp = de;
-    rc = launch_attention(P_FP8, a, s);
-    if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = REVO_EDEVICE;
-  }
-  if (d) (void)hipFree(d);
-  if (work) (void)hipFree(work);
-  if (de) (void)hipFree(de);
+  int rc = launch_attention_one(P_FP8, q8, k8, vt8, o, heads, ntok, ld, he, s);
+  if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = REVO_EDEVICE;
   return rc;
 }
 
@@ -154,8 +102,8 @@ int revo_op_attention_noalloc(int precision, const void* q, const void* k, const
   if (!prec_of(precision, &p)) return REVO_ENOTSUP;
   if (heads <= 0 || ntok <= 0 || ld < ntok + 64 || !q || !k || !vt || !o) return REVO_EINVAL;
   if (ld % 16) return REVO_EINVAL;
-  if ((ntok + 127) / 128 > ATTN_NOALLOC_MAX_TILES) return REVO_E2BIG;
-  return launch_attention_noalloc(p, q, k, vt, o, heads, ntok, ld, (hipStream_t)stream);
+  if ((ntok + 127) / 128 > ATTN_MAX_TILES) return REVO_E2BIG;
+  return launch_attention_one(p, q, k, vt, o, heads, ntok, ld, nullptr, (hipStream_t)stream);
 }
 
 int revo_op_convert(int precision, const float* src, void* dst, long long n, void* stream) {

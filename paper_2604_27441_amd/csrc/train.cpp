@@ -86,7 +86,7 @@ struct revo_trainer {
   int C = 3, T = 2, k = 5, ne = 12, nd = 4, B = 1, H = 0, W = 0;
   int J = 0, gy = 0, gx = 0, P = 0, N = 0, Nal = 0, nfr = 0, Lt = 0;
   int M = 0, Mpad = 0, Mh = 0, Mh_pad = 0, ld = 0;
-  int nwork_f = 0, nwork_b = 0, loss_blocks = 0, max_chunks = 0, ln_blocks = 0;
+  int attn_tile_f = 0, nwork_f = 0, nwork_b = 0, loss_blocks = 0, max_chunks = 0, ln_blocks = 0;
   float lr = 2e-4f, b1 = 0.9f, b2 = 0.999f, eps = 1e-8f, alpha = 0.01f;
   long long step = 0;
   Layout L;
@@ -252,6 +252,7 @@ int block_fwd(revo_trainer* t, const BlockL& b, BlockAct& A, float* xout, int D,
   memset(&at, 0, sizeof(at));
   at.q = A.q; at.k = A.k; at.vt = A.vt; at.o = A.o; at.heads = heads; at.ldqk = t->ld; at.ldv = t->ld;
   at.reqs = t->d_reqs; at.nreq = t->B; at.work = t->d_work_f; at.nwork = t->nwork_f; at.lse = A.lse;
+  at.tile = t->attn_tile_f;
   if ((e = launch_attention(P_FP32, at, s))) return e;
   GemmArgs pr = g;
   pr.X = A.o; pr.K = D; pr.N = D; pr.W = t->theta + b.proj.w; pr.bias = t->theta + b.proj.b;
@@ -492,10 +493,13 @@ int setup(revo_trainer* t, const revo_train_config& c) {
   if (hipMemcpyAsync(t->theta, c.weights, n * 4, hipMemcpyHostToDevice, t->s) != hipSuccess) return REVO_EDEVICE;
   if ((e = alloc_n(t, &t->d_reqs, t->B))) return e;
   t->h_reqs.resize(t->B);
-  // work lists: 128-query tiles (forward attention), 64-row blocks (backward)
+  // work lists: query tiles (forward attention), 64-row blocks (backward)
   std::vector<int> wf, wb, rowmap;
+  // (six heads of 128-query tiles that fill most of the CUs: see attn_tile)
+  t->attn_tile_f = t->B * 6 * cdiv(t->N, 128) >= 160 ? 128 : attn_tile(P_FP32, t->N);
+  const int tile = t->attn_tile_f;
   for (int r = 0; r < t->B; ++r) {
-    for (int q = 0; q * 128 < t->N; ++q) wf.push_back((r << 16) | q);
+    for (int q = 0; q * tile < t->N; ++q) wf.push_back((r << 16) | q);
     for (int q = 0; q * 64 < t->N; ++q) wb.push_back((r << 16) | q);
     for (int p = 0; p < t->P; ++p) rowmap.push_back(r * t->Nal + (t->J - 1) * t->P + p);
   }

@@ -196,6 +196,89 @@ def test_attention(prec, heads, ntok):
             assert np.sqrt(np.mean(err ** 2)) < 4e-3 * np.sqrt(np.mean(ref ** 2)) + 1e-3
 
 
+# both FP32 tile forms (64 queries and four key groups up to 1024 tokens, 128
+# and two beyond): a last key block and rounds of the key groups that are
+# empty, full or partial, a last query tile of one row
+@pytest.mark.parametrize("ntok", [31, 33, 65, 127, 129, 161, 1024, 1025, 1088, 1153])
+def test_attention_fp32_tiles(ntok):
+    heads = 2
+    qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=1.5)
+    o = torch.full((ntok + 1, heads * 64), 7.0, dtype=torch.float32).cuda()
+    rc = _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None)
+    assert rc == 0
+    got = o.double().cpu().numpy()
+    assert (got[ntok] == 7.0).all()
+    for h in range(heads):
+        ref = oracle.attention_head(q64[h], k64[h], v64[h])
+        assert np.abs(got[:ntok, h * 64:(h + 1) * 64] - ref).max() < 2e-5 * np.abs(v64[h]).max()
+
+
+@pytest.mark.parametrize("ntok", [300, 1100])
+def test_attention_fp32_range(ntok):
+    """FP32 operands over the whole range: a key whose scores are -inf counts
+    nothing, an infinite value reaches its dimension alone, and a query whose
+    scores hold a NaN (query 40 meets the infinite key with a zero, query 41
+    is NaN itself) leaves the other rows as they are."""
+    heads = 1
+    qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=1.0)
+    q, k, v = q64[0].copy(), k64[0].copy(), v64[0].copy()
+    q[:, 5] = np.abs(q[:, 5]) + 0.1
+    k[7, 5] = -np.inf                       # every query's score of key 7 is -inf
+    v[9, 3] = np.inf
+    q[40] = 0
+    q[40, 8] = 1e15
+    k[:, 8] = -np.abs(k[:, 8]) - 0.1
+    k[21, 8] = 1e16
+    q[np.arange(ntok) != 40, 8] = 0
+    q[41] = np.nan
+    f = math.log2(math.e) / 8
+    qd[0, :ntok] = torch.tensor((q * f).astype(np.float32)).cuda()
+    kd[0, :ntok] = torch.tensor(k.astype(np.float32)).cuda()
+    vt[0, :, :ntok] = torch.tensor(v.astype(np.float32).T.copy()).cuda()
+    o = torch.zeros((ntok, 64), dtype=torch.float32).cuda()
+    assert _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None) == 0
+    got = o.double().cpu().numpy()
+    q32, k32 = (q * f).astype(np.float32).astype(np.float64) / f, k.astype(np.float32).astype(np.float64)
+    k32[7, 5] = 0
+    rows = (np.arange(ntok) != 40) & (np.arange(ntok) != 41)
+    s = q32[rows] @ k32.T / 8
+    s[:, 7] = -np.inf
+    p = np.exp(s - s.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    v0 = v.copy()
+    v0[9, 3] = 0
+    ref = p @ v0
+    ok = np.arange(64) != 3
+    assert np.isnan(got[40:42]).all()
+    assert np.abs(got[rows][:, ok] - ref[:, ok]).max() < 2e-5 * np.abs(v0).max()
+    assert np.isposinf(got[rows, 3]).all()
+
+
+@pytest.mark.parametrize("ntok", [300, 1100])
+def test_attention_fp32_large_scores(ntok):
+    """Scores past what the split products hold (query 40: 1e30 at key 21,
+    -1e14 and below at the others; query 50: -1e30 everywhere but -1e29 at
+    key 200) give the row of the key with the largest score; the other rows
+    are ordinary."""
+    heads = 1
+    qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=1.0)
+    q, k, v = q64[0].copy(), k64[0].copy(), v64[0]
+    q[:, 8:10] = 0
+    q[40], q[50] = 0, 0
+    q[40, 8], q[50, 9] = 1e15, 1e20
+    k[:, 8], k[21, 8] = -np.abs(k[:, 8]) - 0.5, 1e16
+    k[:, 9], k[200, 9] = -1e11, -1e10
+    f = math.log2(math.e) / 8
+    qd[0, :ntok] = torch.tensor((q * f).astype(np.float32)).cuda()
+    kd[0, :ntok] = torch.tensor(k.astype(np.float32)).cuda()
+    o = torch.zeros((ntok, 64), dtype=torch.float32).cuda()
+    assert _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None) == 0
+    got = o.double().cpu().numpy()
+    ref = oracle.attention_head((q * f).astype(np.float32).astype(np.float64) / f, k.astype(np.float32).astype(np.float64), v)
+    ref[40], ref[50] = v[21], v[200]
+    assert np.abs(got - ref).max() < 2e-5 * np.abs(v).max()
+
+
 @pytest.mark.parametrize("prec", [FP32, BF16])
 @pytest.mark.parametrize("direction,amp", [(1, 60.0), (-1, 60.0), (1, 6.0)])
 def test_attention_drifting_max(prec, direction, amp):
