@@ -68,7 +68,17 @@ __device__ inline float erf_as(float x) {
   return copysignf(r, x);
 }
 
-__device__ inline float gelu_erf(float v) { return 0.5f * v * (1.0f + erf_as(v * 0.70710678118654752f)); }
+// GELU(v) = v Phi(v) as v / (1 + 2^(-v q(v^2))): v q(v^2) is the log2 odds of
+// Phi(v), q its minimax polynomial for the error of v Phi(v) on |v| <= 7 (6.7e-8;
+// beyond, q stays positive and growing, so the result tends to v or 0).  10
+// plain and 2 transcendental instructions per value; v times an erf by A&S
+// 7.1.26 takes 13 and 2 with an error of 2.1e-7.
+__device__ inline float gelu_erf(float v) {
+  const float u = v * v;
+  const float q = fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, 5.209905619e-9f, -3.850448520e-7f), 1.145242752e-5f),
+                                              -1.593893939e-4f), -9.559299434e-5f), 1.048385813e-1f), 2.302207204f);
+  return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-(v * q)));
+}
 // d gelu / dv = Phi(v) + v phi(v)
 __device__ inline float gelu_erf_grad(float v) {
   return 0.5f * (1.0f + erf_as(v * 0.70710678118654752f)) +
@@ -343,7 +353,8 @@ constexpr int epi_stage_bytes() {
 // subtiles of 32 features x 32 tokens.  Waves without a part of the tile
 // (!active, the other k groups of a split) only join the barriers and the
 // row stores, which all NT_ threads of the workgroup share.
-template <class Op, int BN, int EPI, class OutT, int BM_, int NT_, int NS, int MS>
+// BI: the accumulators hold the bias already.
+template <class Op, int BN, int EPI, class OutT, int BM_, int NT_, int NS, int MS, bool BI = false>
 __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (&acc)[NS][MS], int m0, int n0,
                                                      int Mlive, int nreq, int tid, int wn, int wm, uint8_t* smem,
                                                      const EpiCols<NS>& cols, bool active = true) {
@@ -382,7 +393,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           v[e] = SC ? acc[ns][ms][4 * g + e] * cols.s[ns][g][e] + cols.b[ns][g][e]
-                    : acc[ns][ms][4 * g + e] + cols.b[ns][g][e];
+                    : (BI ? acc[ns][ms][4 * g + e] : acc[ns][ms][4 * g + e] + cols.b[ns][g][e]);
         if (EPI == EPI_GELU) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
@@ -727,64 +738,64 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N_ & 15) | ((N_ >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
-// One 128-byte K stage from LDS into the accumulators: all 16 fragment
-// reads, then the products.  BF16: four 32x32x16 steps, lane half h taking
-// chunk 4h + s of step s.  FP8: two 32x32x64 steps, lane half h taking chunks
-// 4s + 2h and 4s + 2h + 1 (32 consecutive k, the layout of the register-staged
-// kernel).  The operand pointers are restrict-qualified, so the reads carry
-// alias scopes and the compiler does not hold them behind the ring's loads
-// still in flight (the kernel orders those with vmcnt waits and barriers).
-template <class Op, int BN>
+// One 128-byte K stage from LDS into the accumulators: all fragment reads,
+// then the products.  BF16: four 32x32x16 steps, lane half h taking chunk 4h +
+// s of step s.  FP8: two 32x32x64 steps, lane half h taking chunks 4s + 2h and
+// 4s + 2h + 1 (32 consecutive k, the layout of the register-staged kernel).
+// The operand pointers are restrict-qualified, so the reads carry alias scopes
+// and the compiler does not hold them behind the ring's loads still in flight
+// (the kernel orders those with vmcnt waits and barriers).
+template <class Op, int NS, int MS>
 __device__ __forceinline__ void gemm_dma_stage(const uint8_t* __restrict__ xb, const uint8_t* __restrict__ wb,
-                                               f32x16 (&acc)[BN / 64][2], int wn, int wm, int half, int l32) {
-  constexpr int NSUB = BN / 64;
-  uint4 wf[4][NSUB], xf[4][2];
+                                               f32x16 (&acc)[NS][MS], int wn, int wm, int half, int l32) {
+  uint4 wf[4][NS], xf[4][MS];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     // chunk read at s: BF16 step s; FP8 step s / 2, part s % 2
     const int ch = sizeof(typename Op::T) == 2 ? half * 4 + s : (s >> 1) * 4 + half * 2 + (s & 1);
 #pragma unroll
-    for (int ns = 0; ns < NSUB; ++ns)
-      wf[s][ns] = *reinterpret_cast<const uint4*>(wb + gswz(wn * (BN / 2) + ns * 32 + l32, ch));
+    for (int ns = 0; ns < NS; ++ns)
+      wf[s][ns] = *reinterpret_cast<const uint4*>(wb + gswz((wn * NS + ns) * 32 + l32, ch));
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
-      xf[s][ms] = *reinterpret_cast<const uint4*>(xb + gswz(wm * 64 + ms * 32 + l32, ch));
+    for (int ms = 0; ms < MS; ++ms)
+      xf[s][ms] = *reinterpret_cast<const uint4*>(xb + gswz((wm * MS + ms) * 32 + l32, ch));
   }
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (sizeof(typename Op::T) == 2) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int ns = 0; ns < NSUB; ++ns)
+      for (int ns = 0; ns < NS; ++ns)
 #pragma unroll
-        for (int ms = 0; ms < 2; ++ms)
+        for (int ms = 0; ms < MS; ++ms)
           Op::mma(acc[ns][ms], __builtin_bit_cast(bf16x8, wf[s][ns]), __builtin_bit_cast(bf16x8, xf[s][ms]));
   } else {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int ns = 0; ns < NSUB; ++ns)
+      for (int ns = 0; ns < NS; ++ns)
 #pragma unroll
-        for (int ms = 0; ms < 2; ++ms)
+        for (int ms = 0; ms < MS; ++ms)
           Op::mma(acc[ns][ms], frag_fp8(wf[2 * s][ns], wf[2 * s + 1][ns]), frag_fp8(xf[2 * s][ms], xf[2 * s + 1][ms]));
   }
 }
 
-// Tile BM_ tokens x BN features, 2 WM_ waves (each 64 x BN/2), NS stages of
-// 128 bytes of K.
-template <class Op, int BN, int EPI, class OutT, int NS, int BM_, int WM_>
-__global__ __launch_bounds__(128 * WM_, 512 / (128 * WM_)) void gemm_dma_kernel(const GemmArgs a) {
+// Tile BM_ tokens x BN features over WM_ x WN_ waves, NST stages of 128 bytes
+// of K, OCC waves per SIMD.
+template <class Op, int BM_, int BN, int WM_, int WN_, int NST, int OCC, int EPI, class OutT>
+__global__ __launch_bounds__(64 * WM_* WN_, OCC) void gemm_dma_kernel(const GemmArgs a) {
   typedef typename Op::T T;
   constexpr int BK = 128 / (int)sizeof(T);  // K per stage
   constexpr int E = 16 / (int)sizeof(T);    // K per 16-byte chunk
-  constexpr int NW = 2 * WM_;                         // waves
+  constexpr int NW = WM_ * WN_;                       // waves
+  constexpr int MS = BM_ / (32 * WM_), NS = BN / (32 * WN_);
   constexpr int XR = BM_ / NW, WR = BN / NW;          // stage rows each wave loads
   constexpr int XI = XR / 8, WI = WR / 8;             // 8-row loads per wave per stage
-  static_assert(XI >= 1 && WI >= 1 && BM_ == 64 * WM_, "tile geometry");
+  static_assert(XI >= 1 && WI >= 1 && MS >= 1 && NS >= 1, "tile geometry");
   constexpr int SX = BM_ * 128, SW = BN * 128;        // bytes per X / W stage
-  constexpr int OPB = NS * (SX + SW);
+  constexpr int OPB = NST * (SX + SW);
   constexpr int EPB = epi_stage_bytes<BN, OutT, BM_>();
-  // X stages at stg + b SX, W stages at stg + NS SX + b SW; the epilogue
+  // X stages at stg + b SX, W stages at stg + NST SX + b SW; the epilogue
   // reuses the whole array
   __shared__ __attribute__((aligned(16))) uint8_t stg[OPB > EPB ? OPB : EPB];
 
@@ -827,38 +838,47 @@ __global__ __launch_bounds__(128 * WM_, 512 / (128 * WM_)) void gemm_dma_kernel(
     _Pragma("unroll") for (int j = 0; j < XI; ++j)                                                       \
       dma16(xrs, stg + (buf_) * SX + (wave * XR + 8 * j) * 128, xo[j], (kt_) * 128);                      \
     _Pragma("unroll") for (int j = 0; j < WI; ++j)                                                       \
-      dma16(wrs, stg + NS * SX + (buf_) * SW + (wave * WR + 8 * j) * 128, wo[j], (kt_) * 128);            \
+      dma16(wrs, stg + NST * SX + (buf_) * SW + (wave * WR + 8 * j) * 128, wo[j], (kt_) * 128);           \
   } while (0)
 
   const int wn = wave / WM_, wm = wave % WM_;
-  f32x16 acc[BN / 64][2];
+  f32x16 acc[NS][MS];
+  EpiCols<NS> cols;  // FP8: in flight during the K loop
+  epi_load_cols<Op, NS>(a, n0, wn, half, cols);
+  // BF16 accumulators start from the bias (one addition per output less in
+  // the epilogue)
+  constexpr bool BI = sizeof(T) == 2;
 #pragma unroll
-  for (int i = 0; i < BN / 64; ++i) { acc[i][0] = f32x16{}; acc[i][1] = f32x16{}; }
-  EpiCols<BN / 64> cols;  // in flight during the K loop
-  epi_load_cols<Op, BN / 64>(a, n0, wn, half, cols);
+  for (int i = 0; i < NS; ++i)
+#pragma unroll
+    for (int j = 0; j < MS; ++j)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[i][j][k] = BI ? cols.b[i][k >> 2][k & 3] : 0.0f;
 
-  // stage k goes to buffer k % NS; loads past the last stage re-read it
-  // into a free buffer, which keeps the wait counts static
+  // stage k goes to buffer k % NST, NST - 1 stages ahead
 #pragma unroll
-  for (int i = 0; i < NS - 1; ++i) REVO_GD_FETCH(i < KT ? i : KT - 1, i);
-  // the ring is unrolled NS times so that every buffer index is a constant
+  for (int i = 0; i < NST - 1; ++i)
+    if (i < KT) REVO_GD_FETCH(i, i);
+  // the ring is unrolled NST times so that every buffer index is a constant
   for (int kt = 0; kt < KT;) {
 #pragma unroll
-    for (int b = 0; b < NS; ++b) {
-      wait_vm<(NS - 2) * (XI + WI)>();  // this wave's part of stage kt is in LDS
+    for (int b = 0; b < NST; ++b) {
+      // this wave's part of stage kt is in LDS (the last stages, with fewer
+      // behind them, wait for all loads)
+      if (NST > 2 && kt + NST - 1 <= KT) wait_vm<(NST - 2) * (XI + WI)>();
+      else wait_vm<0>();
       // every wave's part is, and stage kt-1's buffer is free (a plain
       // barrier: the fence of __syncthreads would also wait for the younger
       // stage loads)
       asm volatile("s_barrier" ::: "memory");
-      REVO_GD_FETCH(kt + NS - 1 < KT ? kt + NS - 1 : KT - 1, (b + NS - 1) % NS);
-      gemm_dma_stage<Op, BN>(stg + b * SX, stg + NS * SX + b * SW, acc, wn, wm, half, l32);
+      if (kt + NST - 1 < KT) REVO_GD_FETCH(kt + NST - 1, (b + NST - 1) % NST);
+      gemm_dma_stage<Op, NS, MS>(stg + b * SX, stg + NST * SX + b * SW, acc, wn, wm, half, l32);
       if (++kt >= KT) break;
     }
   }
-  wait_vm<0>();  // no load still writes LDS when the epilogue reuses it
 #undef REVO_GD_FETCH
-  gemm_epilogue_staged<Op, BN, EPI, OutT, BM_, 128 * WM_, BN / 64, 2>(a, acc, m0, n0, Mlive, nreq, tid, wn, wm, stg,
-                                                                      cols);
+  gemm_epilogue_staged<Op, BN, EPI, OutT, BM_, 64 * NW, NS, MS, BI>(a, acc, m0, n0, Mlive, nreq, tid, wn, wm, stg,
+                                                                    cols);
 }
 
 // ---------------------------------------------------------------------------
@@ -1126,19 +1146,39 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   const long long esz = sizeof(typename Op::T);
   if ((long long)gm * BM * a.K * esz >= (1LL << 31) || (long long)a.N * a.K * esz >= (1LL << 31)) return -22;
   // Dense BF16 products (all but the head) and FP8 products whose K is a
-  // multiple of 128 take the LDS-ring kernel, two stages: 128 x 128 tiles over
-  // 4 waves, or, for 64-wide feature tiles, 256 x 64 tiles over 8 waves
-  // (measured faster on the decoder's products)
+  // multiple of 128 take the LDS-ring kernel, two stages.  Its tile forms give
+  // the same results bit for bit; which is chosen (us on one box, M x N x K):
+  //  64 x 64 on 4 waves while 128-wide tiles would leave most CUs with one
+  //   workgroup or none (3600 x 384 x 1536 BF16 19.0 -> 10.1, FP8 12.6 -> 7.5;
+  //   576 x 384 x 1536 18.0 -> 8.4; 3600 x 1152 x 384, 1026 tiles, 9.0 against 8.4
+  //   with the next form);
+  //  BF16: 128 x 128 on 8 waves of 64 x 32, four waves per SIMD (43200 x 1536 x
+  //   384 GELU 84 -> 82, 3600 x 1152 x 384 8.8 -> 8.4, 10800 x 384 x 1536 25.2 ->
+  //   23.2), but 4 waves of 64 x 64 for the residual epilogue beyond two
+  //   workgroups per CU (43200 x 384 x 384 34.5, 40 on 8 waves);
+  //  FP8, whose stages hold twice the K: 128 x 64 on 4 waves, three workgroups
+  //   per CU (10800 x 384 x 1536 17.2 -> 15.0, 43200 x 1536 x 384 69 -> 65), but
+  //   128 x 128 for large plain stores (86400 x 1152 x 384 62 - 66, 71 at 128 x
+  //   64);
+  //  N not a multiple of 128: 256 x 64 on 8 waves (BF16) or 128 x 64 (FP8)
   constexpr bool RING = XM == X_DENSE && EPI != EPI_HEAD && sizeof(typename Op::T) <= 2;
   if constexpr (RING) {
-    if (sizeof(typename Op::T) == 2 || a.K % 128 == 0) {
-      if (a.N % 128 == 0) {
-        gemm_dma_kernel<Op, 128, EPI, OutT, 2, 128, 2><<<dim3(gm * (a.N / 128)), 256, 0, s>>>(a);
-        return hipGetLastError() == hipSuccess ? 0 : -5;
-      }
+    constexpr bool B16 = sizeof(typename Op::T) == 2;
+    constexpr bool RES = EPI == EPI_RESIDUAL, GEL = EPI == EPI_GELU;
+    if (B16 || a.K % 128 == 0) {
       const int gm2 = cdiv(a.M, 256);
-      if ((long long)gm2 * 256 * a.K * esz >= (1LL << 31)) return -22;
-      gemm_dma_kernel<Op, 64, EPI, OutT, 2, 256, 4><<<dim3(gm2 * (a.N / 64)), 512, 0, s>>>(a);
+      if (a.N % 128 && (long long)gm2 * 256 * a.K * esz >= (1LL << 31)) return -22;
+      const long long t64 = (long long)cdiv(a.M, 64) * (a.N / 64), t128 = (long long)gm * (a.N / 128);
+      if (t64 <= 700)
+        gemm_dma_kernel<Op, 64, 64, 2, 2, 2, 4, EPI, OutT><<<dim3((unsigned)t64), 256, 0, s>>>(a);
+      else if (a.N % 128 && B16)
+        gemm_dma_kernel<Op, 256, 64, 4, 2, 2, 1, EPI, OutT><<<dim3(gm2 * (a.N / 64)), 512, 0, s>>>(a);
+      else if (a.N % 128 || (!B16 && (RES || GEL || t128 < 700)))
+        gemm_dma_kernel<Op, 128, 64, 2, 2, 2, 3, EPI, OutT><<<dim3(gm * (a.N / 64)), 256, 0, s>>>(a);
+      else if (B16 && (!RES || t128 <= 512))
+        gemm_dma_kernel<Op, 128, 128, 2, 4, 2, 4, EPI, OutT><<<dim3((unsigned)t128), 512, 0, s>>>(a);
+      else
+        gemm_dma_kernel<Op, 128, 128, 2, 2, 2, 2, EPI, OutT><<<dim3((unsigned)t128), 256, 0, s>>>(a);
       return hipGetLastError() == hipSuccess ? 0 : -5;
     }
   }

@@ -131,6 +131,42 @@ def test_linear_fp32_range(M, N, K):
     assert np.all(err <= 2e-6 * math.sqrt(K) * rowmax + 2.0 ** -148)
 
 
+# shapes beyond the 64 x 64 tiles: BF16 on 128 x 128 (8 waves; 4 waves for the
+# large residual one) and 256 x 64, FP8 on 128 x 64 and 128 x 128
+@pytest.mark.parametrize("prec,epi,M,N,K", [
+    (BF16, 0, 2501, 1152, 384), (BF16, 2, 2501, 1536, 64), (BF16, 1, 8005, 384, 192), (BF16, 1, 22021, 384, 64), (BF16, 0, 5007, 576, 192),
+    (2, 0, 2501, 1152, 384), (2, 2, 2501, 1536, 128), (2, 1, 8005, 384, 256), (2, 0, 22021, 576, 128), (2, 0, 10001, 1152, 384)])
+def test_linear_tile_forms_agree(prec, epi, M, N, K):
+    """Every tile form of the BF16 and FP8 products gives the bits that the
+    64 x 64 one (taken for a few hundred rows) gives for the same rows."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    x = torch.randn((M, K), generator=g, device="cuda")
+    w = torch.randn((N, K), generator=g, device="cuda") * math.sqrt(2.0 / K)
+    b = 0.1 * torch.randn((N,), generator=g, device="cuda")
+    if prec == BF16:
+        xd, wd = x.bfloat16(), w.bfloat16()
+    else:
+        xd, wd = (x * 64).to(torch.float8_e4m3fn).view(torch.uint8), (w * 64).to(torch.float8_e4m3fn).view(torch.uint8)
+        ws, xs, osc = torch.full((N,), 1 / 64.0, device="cuda"), torch.full((1,), 1 / 64.0, device="cuda"), torch.full((1,), 1 / 64.0, device="cuda")
+    if epi == 1:
+        out = torch.randn((M, N), generator=g, device="cuda")
+    else:
+        out = torch.zeros((M, N), dtype=torch.bfloat16 if prec == BF16 or epi == 0 else torch.uint8, device="cuda")
+    parts = out.clone()
+
+    def call(o, r0, r1):
+        if prec == BF16:
+            return _lib().revo_op_linear(BF16, epi, xd[r0:r1].data_ptr(), wd.data_ptr(), b.data_ptr(), o[r0:r1].data_ptr(), r1 - r0, N, K, None)
+        return _lib().revo_op_linear_fp8(epi, xd[r0:r1].data_ptr(), wd.data_ptr(), ws.data_ptr(), xs.data_ptr(), b.data_ptr(),
+                                         o[r0:r1].data_ptr(), osc.data_ptr(), r1 - r0, N, K, None)
+
+    assert call(out, 0, M) == 0
+    for r0 in range(0, M, 304):
+        assert call(parts, r0, min(M, r0 + 304)) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.uint8), parts.view(torch.uint8))
+
+
 @pytest.mark.parametrize("prec", [FP32, BF16])
 @pytest.mark.parametrize("rows,D", [(1, 384), (1000, 384), (333, 192), (5, 24)])
 def test_layernorm(prec, rows, D):
