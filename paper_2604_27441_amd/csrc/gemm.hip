@@ -333,6 +333,19 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[N
   }
 }
 
+// 16 bytes of an epilogue's output.  BF16 and FP8 outputs are stored
+// non-temporally: a product writes them once and streams through far more of
+// them than the L2s hold, so keeping them there only evicts the operand rows
+// other tiles still read (outputs that are not in the last-level cache yet:
+// 43200 x 1536 x 384 GELU BF16 98.5 -> 80.5 us, 86400 x 1152 x 384 FP8 94 -> 66;
+// the whole BF16 network of four 1280x720 requests 1.5 % faster).  FP32 outputs
+// gain nothing (the pretraining step 0.3 % slower) and are stored plainly.
+template <class OutT>
+__device__ __forceinline__ void store16(void* p, const uint4& v) {
+  if constexpr (sizeof(OutT) <= 2) __builtin_nontemporal_store(__builtin_bit_cast(f32x4, v), reinterpret_cast<f32x4*>(p));
+  else *reinterpret_cast<uint4*>(p) = v;
+}
+
 // LDS bytes of the staged epilogue: a row-major [BM][BN] tile of the output
 // type, or for the V part of the QKV product a transposed [BN][BM] tile
 // (rows padded by 16 bytes).
@@ -442,7 +455,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (
       OutT* dst = (OutT*)a.vt + ((size_t)hd * 64 + dd) * a.ldv + m;
       const OutT* src = reinterpret_cast<const OutT*>(smem + nl * TPV) + c;
       if (m + EO <= Mcol) {
-        *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+        store16<OutT>(dst, *reinterpret_cast<const uint4*>(src));
       } else {
         for (int e = 0; m + e < Mcol; ++e) dst[e] = src[e];
       }
@@ -521,9 +534,9 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmArgs& a, f32x16 (
     if (EPI == EPI_QKV) {
       const int hd = (n - part * D) >> 6, dd = n & 63;
       OutT* dst = (OutT*)(part == 0 ? a.q : a.k) + ((size_t)hd * a.ldqk + m) * 64 + dd;
-      *reinterpret_cast<uint4*>(dst) = val;
+      store16<OutT>(dst, val);
     } else {
-      *reinterpret_cast<uint4*>((OutT*)a.out + (size_t)m * a.ldo + n) = val;
+      store16<OutT>((OutT*)a.out + (size_t)m * a.ldo + n, val);
     }
   }
 }
