@@ -138,6 +138,27 @@ def test_moved_view_small(yaw, pitch, t):
     _check_moved_view(depth, rgb, _pose(yaw, pitch, t), intr, 96, 128)
 
 
+@pytest.mark.parametrize("zoom", [4.0, 1.0, 0.5])
+@pytest.mark.parametrize("H,W", [(17, 65), (35, 130)])
+def test_zoomed_view(zoom, H, W):
+    """A view through intrinsics scaled by `zoom`, pixel centres well inside
+    their targets, so the winners are exact: at 4 the target boxes of whole
+    source tiles (64 x 16) exceed the LDS z-buffer and points go to the
+    z-buffer one by one, at 0.5 four points meet on a target."""
+    B = 2
+    depth = RNG.integers(500, 3000, (B, H, W)).astype(np.uint16)
+    depth[:, ::5, ::3] = 0
+    rgb = RNG.integers(0, 256, (B, H, W, 3)).astype(np.uint8)
+    intr = (float(W), float(W), 0.0, 0.0)
+    Ho, Wo = int(H * zoom) + 3, int(W * zoom) - 2   # the last columns fall outside
+    view = (W * zoom, W * zoom, 0.25 - 0.5 * (zoom < 1), 0.25 - 0.5 * (zoom < 1))
+    pose = np.hstack([np.eye(3), np.zeros((3, 1))])
+    c, d, w = _render(_unproject(depth, intr), rgb, pose, view, Ho, Wo)
+    for b in range(B):
+        rc, rd, rw = oracle.render_view(oracle.unproject(depth[b], intr), rgb[b], pose, view, Ho, Wo)
+        assert np.array_equal(w[b], rw) and np.array_equal(c[b], rc) and np.array_equal(d[b], rd)
+
+
 def test_moved_view_720p():
     rgb, depth = synth.scene_frames(1003, 720, 1280, [4, 5])
     intr = (1280.0, 1280.0, 639.5, 359.5)
