@@ -755,6 +755,24 @@ __device__ __forceinline__ i32x8 load_frag8(const uint8_t* __restrict__ t, int r
   return i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
 }
 
+// Probabilities of one lane (byte j = 16 st + i of its 32, fp8_vt_col order)
+// from the scores relative to the running max, without saturation: an
+// exponent past 8.8 gives the E4M3 NaN (0x7F) or 448 (0x7E).
+__device__ __forceinline__ i32x8 fp8_probs(const f32x16 (&sacc)[2]) {
+  i32x8 pf;
+#pragma unroll
+  for (int st = 0; st < 2; ++st)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      float p[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(sacc[st][4 * g + e]);
+      int v = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], 0, false);
+      pf[st * 4 + g] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], v, true);
+    }
+  return pf;
+}
+
 template <bool MASK, bool FIRST>
 __device__ __forceinline__ void fp8_block(const uint8_t* __restrict__ kt, const uint8_t* __restrict__ vt,
                                           const i32x8& qf, const i32x8& ones, f32x16 (&oacc)[2], f32x16& lacc,
@@ -775,15 +793,19 @@ __device__ __forceinline__ void fp8_block(const uint8_t* __restrict__ kt, const 
       for (int i = 0; i < 16; ++i)
         if (st * 32 + acc_row(i, lane) >= kvalid) sacc[st][i] = NEG_BIG;
   }
-  float m0 = fmaxf(fmaxf(sacc[0][0], sacc[0][1]), sacc[0][2]);
-  float m1 = fmaxf(fmaxf(sacc[1][0], sacc[1][1]), sacc[1][2]);
+  auto block_max = [&]() {
+    float m0 = fmaxf(fmaxf(sacc[0][0], sacc[0][1]), sacc[0][2]);
+    float m1 = fmaxf(fmaxf(sacc[1][0], sacc[1][1]), sacc[1][2]);
 #pragma unroll
-  for (int i = 3; i < 15; i += 2) {
-    m0 = fmaxf(fmaxf(m0, sacc[0][i]), sacc[0][i + 1]);
-    m1 = fmaxf(fmaxf(m1, sacc[1][i]), sacc[1][i + 1]);
-  }
-  const float mloc = xhalf_max(fmaxf(fmaxf(m0, sacc[0][15]), fmaxf(m1, sacc[1][15])));
+    for (int i = 3; i < 15; i += 2) {
+      m0 = fmaxf(fmaxf(m0, sacc[0][i]), sacc[0][i + 1]);
+      m1 = fmaxf(fmaxf(m1, sacc[1][i]), sacc[1][i + 1]);
+    }
+    return xhalf_max(fmaxf(fmaxf(m0, sacc[0][15]), fmaxf(m1, sacc[1][15])));
+  };
+  i32x8 pf;
   if constexpr (FIRST) {
+    const float mloc = block_max();
     m_run = mloc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) negm[i] = -mloc;
@@ -791,41 +813,40 @@ __device__ __forceinline__ void fp8_block(const uint8_t* __restrict__ kt, const 
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int i = 0; i < 16; ++i) sacc[st][i] -= mloc;
+    pf = fp8_probs(sacc);
   } else {
-    // mloc is relative to m_run: raise the max only past LAZY
-    const bool grow = mloc > LAZY;
-    if (__any(grow)) {
-      const float d = grow ? mloc : 0.0f;
-      const float alpha = __builtin_amdgcn_exp2f(-d);
-      m_run += d;
-      oacc[0] *= alpha;
-      oacc[1] *= alpha;
-      lacc *= alpha;
+    // The max is raised only past LAZY, that is when a probability exceeds
+    // 2^8: first the probabilities as they are, then a look at their bytes (one
+    // of 0x78 = 256 or above carries into bit 7 when 8 is added: 12 operations
+    // where the block max takes 23), and only then the block max itself.  24
+    // heads x 10800 tokens: 453 -> 441 us, bit-identical (VALU-bound: 32 exp2 a
+    // block and lane are about 2/3 of that).
+    static_assert(LAZY == 8.0f, "0x78 is 2^8");
+    pf = fp8_probs(sacc);
+    unsigned big = 0;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) negm[i] = -m_run;
+    for (int j = 0; j < 8; ++j) big |= (unsigned)pf[j] + 0x08080808u;
+    if (__any((big & 0x80808080u) != 0)) {
+      const float mloc = block_max();  // relative to m_run
+      const bool grow = mloc > LAZY;
+      if (__any(grow)) {
+        const float d = grow ? mloc : 0.0f;
+        const float alpha = __builtin_amdgcn_exp2f(-d);
+        m_run += d;
+        oacc[0] *= alpha;
+        oacc[1] *= alpha;
+        lacc *= alpha;
 #pragma unroll
-      for (int st = 0; st < 2; ++st)
+        for (int i = 0; i < 16; ++i) negm[i] = -m_run;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[st][i] -= d;
-      asm volatile("" : "+v"(oacc[0]), "+v"(oacc[1]), "+v"(lacc), "+v"(sacc[0]), "+v"(sacc[1]), "+v"(negm));
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sacc[st][i] -= d;
+        pf = fp8_probs(sacc);
+        asm volatile("" : "+v"(oacc[0]), "+v"(oacc[1]), "+v"(lacc), "+v"(negm), "+v"(pf));
+      }
     }
   }
-  // probabilities: byte j = 16 st + i of the lane's 32 (fp8_vt_col order).
-  // Every exponent is at most LAZY = 8, so p lies in [0, 256], inside the
-  // E4M3 range: the conversion needs no saturation (the clamp to +-448 would
-  // change no value)
-  static_assert(LAZY <= 8.0f, "probabilities below the E4M3 maximum");
-  i32x8 pf;
-#pragma unroll
-  for (int st = 0; st < 2; ++st)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float p[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(sacc[st][4 * g + e]);
-      int v = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], 0, false);
-      pf[st * 4 + g] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], v, true);
-    }
 #pragma unroll
   for (int ds = 0; ds < 2; ++ds) oacc[ds] = mfma_fp8(load_frag8(vt, ds * 32 + l32, half), pf, oacc[ds], ev, 127);
   // row sums of the E4M3 probabilities on the matrix core: a block whose

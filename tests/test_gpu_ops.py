@@ -549,3 +549,35 @@ def test_attention_fp8(heads, ntok):
               f"max {np.abs(e_gpu).max():.3g} (oracle {np.abs(e_emu).max():.3g})")
         assert rms <= np.sqrt(2.0) * rms_emu, (h, rms, rms_emu)
         assert np.abs(e_gpu).max() <= 4.0 * np.abs(e_emu).max(), h
+
+
+@pytest.mark.parametrize("amp,ntok", [(4.0, 700), (30.0, 700), (-30.0, 700), (4.0, 65)])
+def test_attention_fp8_drifting_max(amp, ntok):
+    """Scores that rise over the keys by about 7 or 50 log2 units (or fall by
+    50): probabilities pass 2^8 never, many times, or never, each time the
+    running max is raised and the block's probabilities taken again.  Against
+    FP64 attention on the rounded operands, within the FP8-rounding oracle's
+    budget (twice its MSE, four times its max error)."""
+    rng = np.random.default_rng(77)
+    c = oracle.QK_LOG2
+    ld = (ntok + 64 + 63) // 64 * 64
+    q, k, v = (rng.standard_normal((ntok, 64)) for _ in range(3))
+    q[:, 0] += 10.0
+    k[:, 0] += amp * np.linspace(0.0, 1.0, ntok)
+    sc = [oracle.pow2_scale(np.abs(x).max() / 448) for x in (q * c, k, v)]
+    ex = np.array([int(round(math.log2(s))) for s in sc], dtype=np.int32)
+    q8, k8 = (torch.zeros((1, ld, 64), dtype=torch.uint8) for _ in range(2))
+    vt8 = torch.zeros((1, 64, ld), dtype=torch.uint8)
+    q8[0, :ntok], k8[0, :ntok] = _e4m3_bytes(q * c / sc[0]), _e4m3_bytes(k / sc[1])
+    vt8[0][:, torch.from_numpy(_fp8_vt_col(np.arange(ntok)))] = _e4m3_bytes(v / sc[2]).T.contiguous()
+    qr = oracle.e4m3_round(q * c / sc[0]) * sc[0] / c
+    kr, vr = oracle.e4m3_round(k / sc[1]) * sc[1], oracle.e4m3_round(v / sc[2]) * sc[2]
+    o = torch.zeros((ntok, 64), dtype=torch.bfloat16).cuda()
+    qd, kd, vd = q8.cuda(), k8.cuda(), vt8.cuda()
+    assert _lib().revo_op_attention_fp8(qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), o.data_ptr(), 1, ntok, ld, ex.ctypes.data, None) == 0
+    exact = oracle.attention_head(qr, kr, vr)
+    emu = oracle.attention_head(qr, kr, vr, rnd=oracle.FP8Rounding({}), site="x.attn.p")
+    e_gpu, e_emu = o.double().cpu().numpy() - exact, emu - exact
+    bf16 = 2.0 ** -8 * np.abs(exact)          # the output's own rounding
+    assert np.sqrt(np.mean(e_gpu ** 2)) <= np.sqrt(2.0) * np.sqrt(np.mean(e_emu ** 2)) + np.sqrt(np.mean(bf16 ** 2))
+    assert np.abs(e_gpu).max() <= 4.0 * np.abs(e_emu).max() + bf16.max()
