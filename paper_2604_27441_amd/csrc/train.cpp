@@ -145,9 +145,9 @@ int weight_grad(revo_trainer* t, const float* dy, const float* x, int Mrows, con
   int e;
   const int tiles = cdiv(l.out, 128) * cdiv(l.in, 128);
   int S = 512 / tiles;
-  if (S > Mrows / 64) S = Mrows / 64;  // at least 64 rows (4 stages) per chunk
+  if (S > Mrows / 64) S = Mrows / 64;  // at least 64 rows (2 stages) per chunk
   if (S < 1) S = 1;
-  const int kc = align_up(cdiv(Mrows, S), 16);
+  const int kc = align_up(cdiv(Mrows, S), 32);  // whole stages
   S = cdiv(Mrows, kc);
   const long long nw = (long long)l.out * l.in;
   if (S == 1) return launch_wgrad(dy, x, Mrows, l.out, l.in, l.out, l.in, kc, 1, gblob + l.w, nw, gblob + l.b, 0, t->s2);
@@ -177,9 +177,9 @@ int weight_grad2(revo_trainer* t, const float* dy0, const float* x0, const Lin& 
   int tiles = 0;
   for (const Lin* l : L) tiles += cdiv(l->out, 128) * cdiv(l->in, 128);
   int S = 512 / tiles;
-  if (S > Mrows / 64) S = Mrows / 64;  // at least 64 rows (4 stages) per chunk
+  if (S > Mrows / 64) S = Mrows / 64;  // at least 64 rows (2 stages) per chunk
   if (S < 1) S = 1;
-  const int kc = align_up(cdiv(Mrows, S), 16);
+  const int kc = align_up(cdiv(Mrows, S), 32);  // whole stages
   S = cdiv(Mrows, kc);
   WgradJob w[2];
   const float* dys[2] = {dy0, dy1};

@@ -116,11 +116,20 @@ __global__ __launch_bounds__(TB) void colsum_final_kernel(const float* __restric
 // the first input columns also write bpart[c][o] = the same rows' sum of
 // dy[m][o].  Both operands are read as they lie (token rows, features
 // contiguous), so no transposed copies are made.  Tile 128 (o) x 128 (i) on
-// 4 waves of 64 x 64 (2 x 2 FP32 32x32x2 MFMA blocks); stages of 16 rows of
-// each operand double-buffered in LDS, the next stage fetched into registers
-// during the current one's products.  One launch can hold two layers over
-// the same rows (independent products of one block's backward pass): the
-// tiles from tile1 on belong to the second.
+// 4 waves of 64 x 64.  The FP32 products run on the BF16 matrix cores: every
+// value times 2^24 is split exactly into three BF16 parts (common.h split3) and
+// the six largest of the nine products of two values' parts are accumulated in
+// FP32; a wave that ends with a non-finite accumulator repeats its part with
+// FP32 MFMAs (see gemm_f32_kernel).  Stages of 32 rows are fetched into
+// registers during the previous stage's products; on the way into LDS four rows
+// of a feature become 8 contiguous bytes of that feature's row in each part's
+// plane, so that a lane's eight rows of an operand are one 16-byte read.  What
+// bounds it is the matrix cores' rate at the clock of this load; the launches of
+// a 256x192 batch-8 step beside the input-gradient chain: 75.6 -> 60.0 us on
+// average (FP32 MFMAs before), the step 12.17 -> 11.57 ms with the gradients
+// copied out.
+// One launch can hold two layers over the same rows (independent products of
+// one block's backward pass): the tiles from tile1 on belong to the second.
 struct WgradLayer {
   const float* dy;
   const float* x;
@@ -135,9 +144,19 @@ struct WgradArgs {
   int rows, kc;
 };
 
+// Byte of 16-byte chunk c (rows 8 c .. 8 c + 7 of the stage) of feature f in a
+// plane: 64 bytes per feature, four features to 256 bytes, whose 16 chunks are
+// permuted by the index of that group of four.  The 64 stores of a wave (16
+// groups, both halves of a chunk) and the 16 features of a read phase each
+// cover all banks.
+__device__ __forceinline__ int wg_chunk(int f, int c) {
+  return (f >> 2) * 256 + ((((f & 3) * 4 + c) ^ ((f >> 2) & 15)) << 4);
+}
+
 __global__ __launch_bounds__(TB, 2) void wgrad_kernel(const WgradArgs args) {
-  constexpr int R = 16, P = 160;  // rows per stage; row pitch (half-waves read rows 2s and 2s + 1 on disjoint banks)
-  __shared__ __attribute__((aligned(16))) float sy[2][R][P], sx[2][R][P];
+  constexpr int R = 32;              // rows per stage
+  constexpr int PB = 128 * R * 2;    // bytes per plane
+  __shared__ __attribute__((aligned(16))) uint8_t smem[6 * PB];  // dy parts, then x parts
   // Workgroups go round-robin to the 8 XCDs, each with its own L2: give XCD
   // x a contiguous range of (chunk, tile) pairs, tile fastest, so the tiles
   // that read one chunk's rows share that XCD's L2 instead of every L2
@@ -154,62 +173,111 @@ __global__ __launch_bounds__(TB, 2) void wgrad_kernel(const WgradArgs args) {
   const int m0 = chunk * args.kc, m1 = min(args.rows, m0 + args.kc);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
   const int wo = wave >> 1, wi = wave & 1;
-  // loader: rows tid / 32 and tid / 32 + 8 of the stage, columns 4 (tid %
-  // 32) .. +3 of the tile, so the 32 lanes of a half-wave move 512
-  // contiguous bytes of one row (coalesced loads, conflict-free LDS stores).
-  // Buffer loads: the descriptors end at the chunk's last row, so rows past
-  // it read as zeros without a branch.  Columns past the matrix (a partial
-  // last tile) read the next row or zeros; they only reach outputs and bias
-  // sums that are not stored.
-  const int lr = tid >> 5, lc = (tid & 31) * 4;
+  // loader: rows 4 t .. 4 t + 3 of the stage (t = 2 wave + tid % 2), columns 4
+  // fq .. +3 of the tile (fq = tid / 2 % 32), so a wave's load moves 512
+  // contiguous bytes of each of two rows.  Buffer loads: the descriptors end at
+  // the chunk's last row, so rows past it read as zeros without a branch.
+  // Columns past the matrix (a partial last tile) read the next row or zeros;
+  // they only reach outputs and bias sums that are not stored.
+  const int sub = tid & 1, fq = (tid >> 1) & 31, lr = 4 * (2 * wave + sub);
   const __amdgpu_buffer_rsrc_t yrs =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.dy, (short)0, m1 * a.ldy * (int)sizeof(float), 0x00020000);
   const __amdgpu_buffer_rsrc_t xrs =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.x, (short)0, m1 * a.ldx * (int)sizeof(float), 0x00020000);
   const bool bias = a.bpart && i0 == 0;
-  float4 ry[2], rx[2];
+  float4 ry[4], rx[4];
   float bs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   auto fetch = [&](int r0) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int m = r0 + lr + 8 * h;
-      const int yo = (m * a.ldy + o0 + lc) * (int)sizeof(float), xo = (m * a.ldx + i0 + lc) * (int)sizeof(float);
+    for (int h = 0; h < 4; ++h) {
+      const int m = r0 + lr + h;
+      const int yo = (m * a.ldy + o0 + 4 * fq) * (int)sizeof(float), xo = (m * a.ldx + i0 + 4 * fq) * (int)sizeof(float);
       ry[h] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(yrs, yo, 0, 0));
       rx[h] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xo, 0, 0));
     }
   };
-  auto put = [&](int b) {
+  auto put_feature = [&](uint8_t* base, int e, float v0, float v1, float v2, float v3) {
+    uint2 p[3];
+    split3x4(make_float4(v0, v1, v2, v3), p);
+    const int at = wg_chunk(4 * fq + e, wave) + sub * 8;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      *reinterpret_cast<float4*>(&sy[b][lr + 8 * h][lc]) = ry[h];
-      *reinterpret_cast<float4*>(&sx[b][lr + 8 * h][lc]) = rx[h];
-      if (bias) { bs[0] += ry[h].x; bs[1] += ry[h].y; bs[2] += ry[h].z; bs[3] += ry[h].w; }
-    }
+    for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(base + j * PB + at) = p[j];
+  };
+  auto put_rows = [&](uint8_t* base, const float4 (&r)[4]) {
+    put_feature(base, 0, r[0].x, r[1].x, r[2].x, r[3].x);
+    put_feature(base, 1, r[0].y, r[1].y, r[2].y, r[3].y);
+    put_feature(base, 2, r[0].z, r[1].z, r[2].z, r[3].z);
+    put_feature(base, 3, r[0].w, r[1].w, r[2].w, r[3].w);
   };
   f32x16 acc[2][2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) { acc[u][0] = f32x16{}; acc[u][1] = f32x16{}; }
   const int nst = (m1 - m0 + R - 1) / R;
-  if (nst > 0) {
-    fetch(m0);
-    put(0);
-  }
-  __syncthreads();
+  if (nst > 0) fetch(m0);
   for (int st = 0; st < nst; ++st) {
-    const int b = st & 1;
-    if (st + 1 < nst) fetch(m0 + (st + 1) * R);
+    if (st > 0) __syncthreads();  // the previous stage is consumed
+    put_rows(smem, ry);
+    put_rows(smem + 3 * PB, rx);
+    if (bias) {
 #pragma unroll
-    for (int k = 0; k < R / 2; ++k) {
-      const int r = 2 * k + half;
-      const float y0 = sy[b][r][64 * wo + l32], y1 = sy[b][r][64 * wo + 32 + l32];
-      const float x0 = sx[b][r][64 * wi + l32], x1 = sx[b][r][64 * wi + 32 + l32];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, x0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, x1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, x0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, x1, acc[1][1], 0, 0, 0);
+      for (int h = 0; h < 4; ++h) { bs[0] += ry[h].x; bs[1] += ry[h].y; bs[2] += ry[h].z; bs[3] += ry[h].w; }
     }
-    if (st + 1 < nst) put(b ^ 1);
     __syncthreads();
+    if (st + 1 < nst) fetch(m0 + (st + 1) * R);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      bf16x8 yf[3][2], xf[3][2];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          yf[j][u] = *reinterpret_cast<const bf16x8*>(smem + j * PB + wg_chunk(64 * wo + 32 * u + l32, 2 * s + half));
+          xf[j][u] =
+              *reinterpret_cast<const bf16x8*>(smem + (3 + j) * PB + wg_chunk(64 * wi + 32 * u + l32, 2 * s + half));
+        }
+      // smallest products first
+#pragma unroll
+      for (int p = 0; p < 6; ++p) {
+        constexpr int PY[6] = {0, 2, 1, 0, 1, 0}, PX[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 2; ++v) OpBF16::mma(acc[u][v], yf[PY[p]][u], xf[PX[p]][v]);
+      }
+    }
+  }
+  {
+    float t = 0.0f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t = fmaf(acc[u][v][j], 0.0f, t);
+    if (__any(t != 0.0f)) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) { acc[u][0] = f32x16{}; acc[u][1] = f32x16{}; }
+#pragma unroll 1
+      for (int m = m0; m < m1; m += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float yv = __builtin_bit_cast(
+              float, __builtin_amdgcn_raw_buffer_load_b32(yrs, ((m + half) * a.ldy + o0 + 64 * wo + 32 * u + l32) * 4, 0, 0));
+#pragma unroll
+          for (int v = 0; v < 2; ++v) {
+            const float xv = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(xrs, ((m + half) * a.ldx + i0 + 64 * wi + 32 * v + l32) * 4, 0, 0));
+            acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(yv, xv, acc[u][v], 0, 0, 0);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] *= 0x1p-48f;
+    }
   }
   float* out = a.part + (size_t)chunk * a.pstride;
 #pragma unroll
@@ -225,11 +293,11 @@ __global__ __launch_bounds__(TB, 2) void wgrad_kernel(const WgradArgs args) {
       }
     }
   if (bias) {
-    // the 8 loader rows' sums of each column (rows r and r + 8 of every
-    // stage), added in row order
-    float* red = &sx[0][0][0];  // [8][128]: free after the last barrier
+    // the 8 loader row groups' sums of each column, added in order
+    float* red = reinterpret_cast<float*>(smem);  // [8][128]
+    __syncthreads();  // every wave is done with the last stage
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[lr * 128 + lc + e] = bs[e];
+    for (int e = 0; e < 4; ++e) red[(2 * wave + sub) * 128 + 4 * fq + e] = bs[e];
     __syncthreads();
     if (tid < 128 && o0 + tid < a.nout) {
       float t = 0.0f;
