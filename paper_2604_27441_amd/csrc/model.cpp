@@ -217,15 +217,27 @@ int workspace_alloc(Workspace& w, const ModelW& m, int cap, int max_req, hipStre
   rc |= get(&w.hid, (size_t)cap * 4 * De * e);
   rc |= get((void**)&w.z, (size_t)cap * m.Dd * 4);
   rc |= get(&w.ahead, (size_t)cap * m.Dd * e);
-  rc |= get((void**)&w.d_reqs, (size_t)max_req * sizeof(ReqDesc));
-  rc |= get((void**)&w.d_work, 2 * (size_t)w.max_work * 4);  // all q-tiles, then target-tubelet q-tiles
-  rc |= get((void**)&w.d_hdr, HDR_N * 4);
+  // a batch's descriptors, one block on either side so that one copy moves
+  // them: header, requests, target-tubelet q-tiles, all q-tiles
+  const size_t req_at = HDR_N * 4, last_at = req_at + (size_t)max_req * sizeof(ReqDesc);
+  const size_t work_at = last_at + (size_t)w.max_work * 4, desc_bytes = work_at + (size_t)w.max_work * 4;
+  static_assert(HDR_N * 4 % alignof(ReqDesc) == 0 && sizeof(ReqDesc) % 4 == 0, "descriptor block alignment");
+  char* d = nullptr;
+  rc |= get((void**)&d, desc_bytes);
   if (rc) return rc < 0 ? rc : -5;
+  w.d_hdr = (int*)d;
+  w.d_reqs = (ReqDesc*)(d + req_at);
+  w.d_work_last = (int*)(d + last_at);
+  w.d_work = (int*)(d + work_at);
+  w.work_at = work_at;
   for (int sl = 0; sl < WS_SLOTS; ++sl) {
-    REVO_HIP_TRY(hipHostMalloc((void**)&w.h_reqs_slot[sl], (size_t)max_req * sizeof(ReqDesc), hipHostMallocDefault));
-    REVO_HIP_TRY(hipHostMalloc((void**)&w.h_work_slot[sl], 2 * (size_t)w.max_work * 4, hipHostMallocDefault));
-    REVO_HIP_TRY(hipHostMalloc((void**)&w.h_hdr_slot[sl], HDR_N * 4, hipHostMallocDefault));
-    memset(w.h_reqs_slot[sl], 0, (size_t)max_req * sizeof(ReqDesc));
+    char* h = nullptr;
+    REVO_HIP_TRY(hipHostMalloc((void**)&h, desc_bytes, hipHostMallocDefault));
+    memset(h, 0, desc_bytes);
+    w.h_hdr_slot[sl] = (int*)h;
+    w.h_reqs_slot[sl] = (ReqDesc*)(h + req_at);
+    w.h_work_last_slot[sl] = (int*)(h + last_at);
+    w.h_work_slot[sl] = (int*)(h + work_at);
   }
   w.h_reqs = w.h_reqs_slot[0];
   REVO_HIP_TRY(hipStreamSynchronize(s));
@@ -236,14 +248,11 @@ void workspace_free(Workspace& w) {
   prof_free(w.prof);
   for (auto& g : w.graph)
     if (g) (void)hipGraphExecDestroy(g);
-  void* dev[] = {w.h, w.a, w.q, w.k, w.vt, w.o, w.hid, w.z, w.ahead, w.d_reqs, w.d_work, w.d_hdr};
+  void* dev[] = {w.h, w.a, w.q, w.k, w.vt, w.o, w.hid, w.z, w.ahead, w.d_hdr};
   for (void* p : dev)
     if (p) (void)hipFree(p);
-  for (int sl = 0; sl < WS_SLOTS; ++sl) {
-    if (w.h_reqs_slot[sl]) (void)hipHostFree(w.h_reqs_slot[sl]);
-    if (w.h_work_slot[sl]) (void)hipHostFree(w.h_work_slot[sl]);
+  for (int sl = 0; sl < WS_SLOTS; ++sl)
     if (w.h_hdr_slot[sl]) (void)hipHostFree(w.h_hdr_slot[sl]);
-  }
   w = Workspace();
 }
 
@@ -332,7 +341,7 @@ int enqueue_net(const ModelW& m, Workspace& w, int Mg, int Mhg, int nworkg, int 
       ab.o_scale = fp8 ? m.act_scale + sp : nullptr;
       ab.qkv_exp = fp8 ? m.attn_exp + ao : nullptr;
       if (last) {
-        ab.work = w.d_work + w.max_work;
+        ab.work = w.d_work_last;
         ab.nwork = nworkg_last;
         ab.dyn_nwork = H ? H + HDR_NWORK_LAST : nullptr;
       }
@@ -401,7 +410,7 @@ int forward(const ModelW& m, Workspace& w, int slot, int nrec, int nall, int com
   int M = 0, Mh = 0, nwork = 0, max_pix = 0;
   double Mreal = 0.0, attn_pairs = 0.0, attn_pairs_last = 0.0;
   int nwork_last = 0;
-  int* work_last = work + w.max_work;
+  int* work_last = w.h_work_last_slot[slot];
   for (int r = 0; r < nall; ++r) {
     ReqDesc& d = reqs[r];
     d.gy = cdiv(d.H, REVO_PATCH);
@@ -434,11 +443,7 @@ int forward(const ModelW& m, Workspace& w, int slot, int nrec, int nall, int com
   if (M > w.cap) return -22;
   hdr[HDR_M] = M; hdr[HDR_MH] = Mh; hdr[HDR_NREC] = nrec; hdr[HDR_NALL] = nall; hdr[HDR_NWORK] = nwork;
   hdr[HDR_NWORK_LAST] = nwork_last;
-  REVO_HIP_TRY(hipMemcpyAsync(w.d_reqs, reqs, (size_t)nall * sizeof(ReqDesc), hipMemcpyHostToDevice, s));
-  REVO_HIP_TRY(hipMemcpyAsync(w.d_hdr, hdr, HDR_N * 4, hipMemcpyHostToDevice, s));
-  if (nwork > 0) REVO_HIP_TRY(hipMemcpyAsync(w.d_work, work, (size_t)nwork * 4, hipMemcpyHostToDevice, s));
-  if (nwork_last > 0)
-    REVO_HIP_TRY(hipMemcpyAsync(w.d_work + w.max_work, work_last, (size_t)nwork_last * 4, hipMemcpyHostToDevice, s));
+  REVO_HIP_TRY(hipMemcpyAsync(w.d_hdr, hdr, w.work_at + (size_t)nwork * 4, hipMemcpyHostToDevice, s));
 
   if (!use_graph || w.prof.on || record) {
     return enqueue_net(m, w, M, Mh, nwork, nwork_last, nrec, nall, max_pix, composite, false, Mreal, Mh, attn_pairs,

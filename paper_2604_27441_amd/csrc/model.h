@@ -84,12 +84,15 @@ struct Workspace {
   float* h = nullptr;
   void *a = nullptr, *q = nullptr, *k = nullptr, *vt = nullptr, *o = nullptr, *hid = nullptr, *ahead = nullptr;
   float* z = nullptr;
-  ReqDesc* d_reqs = nullptr;
-  int* d_work = nullptr;
+  // a batch's descriptors: one device block and, per batch in flight, one
+  // pinned host block of the same layout (header first, all q-tiles last)
   int* d_hdr = nullptr;                  // live batch shape (BatchHdr)
-  ReqDesc* h_reqs_slot[WS_SLOTS] = {};   // pinned host descriptors, one set per batch in flight
-  int* h_work_slot[WS_SLOTS] = {};
+  ReqDesc* d_reqs = nullptr;
+  int *d_work_last = nullptr, *d_work = nullptr;  // target-tubelet q-tiles, all q-tiles
+  size_t work_at = 0;                    // byte of d_work in the block
   int* h_hdr_slot[WS_SLOTS] = {};
+  ReqDesc* h_reqs_slot[WS_SLOTS] = {};
+  int *h_work_last_slot[WS_SLOTS] = {}, *h_work_slot[WS_SLOTS] = {};
   ReqDesc* h_reqs = nullptr;             // = h_reqs_slot[0] (single-batch callers)
   hipGraphExec_t graph[WS_BUCKETS] = {};
   size_t bytes = 0;
