@@ -98,12 +98,20 @@ __device__ inline uint32_t bf16_pack(float a, float b) {
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
 __device__ inline void split3(float a, float b, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
+  // what is left of a (b) is a plus the pair's dot product with (-1, 0) ((0,
+  // -1)): one instruction where unpacking and subtracting take two; both
+  // differences are exact
+  // (the constants pass through registers: an inline constant does not mean
+  // this pair to the instruction)
+  uint32_t lo_ = 0x0000BF80u, hi_ = 0xBF800000u;
+  asm("" : "+s"(lo_), "+s"(hi_));
+  const bf16x2 lo = __builtin_bit_cast(bf16x2, lo_), hi = __builtin_bit_cast(bf16x2, hi_);
   p0 = bf16_pack(a, b);
-  a -= __uint_as_float(p0 << 16);
-  b -= __uint_as_float(p0 & 0xFFFF0000u);
+  a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p0), lo, a, false);
+  b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p0), hi, b, false);
   p1 = bf16_pack(a, b);
-  a -= __uint_as_float(p1 << 16);
-  b -= __uint_as_float(p1 & 0xFFFF0000u);
+  a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p1), lo, a, false);
+  b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p1), hi, b, false);
   p2 = bf16_pack(a, b);
 }
 __device__ inline void split3x4(const float4& v, uint2 (&p)[3]) {
