@@ -407,10 +407,11 @@ __global__ __launch_bounds__(NT, 3) void attn_kernel(const AttnArgs a) {
 // accumulated in FP32 on the BF16 matrix cores: 6 products at 16 times the
 // rate of the FP32 MFMA.  KG groups of QW waves (32 queries each) take every
 // KG-th key block, each with its own running max, row sum and output, which
-// are merged through LDS at the end; so a tile of 32 QW queries keeps two
-// waves on every SIMD.  K and V^T blocks go through registers (fetched one
-// round ahead), are split once per workgroup and lie in LDS as one BF16 plane
-// per part.
+// are merged through LDS at the end.  K and V^T blocks go through registers
+// (fetched one round ahead), are split once per group and lie in LDS as one
+// BF16 plane per part.  Large requests take 4 waves x 2 groups (128 queries,
+// two waves on every SIMD), small ones 1 wave x 6 groups (32 queries), whose
+// waves share nothing until the merge and so need no barriers.
 //
 // The scores come out times 2^48 and the probabilities times 2^24, both undone
 // for free (the shift by the max is a multiply-add; the output divides by a
@@ -481,18 +482,20 @@ __device__ __forceinline__ int f32_plane(int r, int c) {
 }
 
 constexpr int F32_NT = 512;       // threads per workgroup
-constexpr int F32_LDS = 98304;    // K and V^T planes of one block per key group
+constexpr int F32_LDS = 147456;   // K and V^T planes of one block per key group
 
 template <int QW, int KG, int KBF>
 __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem& it, uint8_t* smem) {
-  static_assert(64 * QW * KG == F32_NT, "eight waves");
+  static_assert(64 * QW * KG <= F32_NT, "at most eight waves (the others only join the barriers)");
   constexpr int GT = 64 * QW;               // threads of a key group
   constexpr int KP = KBF * 128, VP = 64 * KBF * 2;  // bytes per K / V^T plane
   constexpr int GB = 3 * (KP + VP);
   static_assert(KG * GB <= F32_LDS, "LDS");
   constexpr int LC = KBF * 16 / GT;         // 16-byte chunks per thread of K and of V^T
   constexpr int NST = KBF / 32;             // 32-key subtiles per block
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // (scalar, so that the block offsets of the loads and the bounds checks are)
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, l32 = lane & 31;
   const int kg = wave / QW, qw = wave % QW, gt = tid - kg * GT;
   const int hd = it.hd, N = it.N, base = it.base, q0 = it.q0;
@@ -554,13 +557,23 @@ __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem&
   oacc[0] = f32x16{};
   oacc[1] = f32x16{};
   float m_run = NEG_BIG, l_run = 0.0f;
-  const int nkb = (N + KBF - 1) / KBF, rounds = (nkb + KG - 1) / KG;
-  fetch(kg * KBF);
+  // a group of one wave orders its LDS stores and reads by itself
+  auto group_sync = [&]() {
+    if constexpr (QW == 1) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    } else {
+      __syncthreads();
+    }
+  };
+  static_assert(QW == 1 || 64 * QW * KG == F32_NT, "barriers need every wave in the loop");
+  const int nkb = (N + KBF - 1) / KBF, rounds = kg < KG ? (nkb + KG - 1) / KG : 0;
+  if (rounds > 0) fetch(kg * KBF);
   for (int t = 0; t < rounds; ++t) {
     const int kb = (t * KG + kg) * KBF;
-    if (t > 0) __syncthreads();  // the previous block is consumed
+    if (t > 0) group_sync();  // the previous block is consumed
     land();
-    __syncthreads();
+    group_sync();
     if (t + 1 < rounds) fetch(kb + KG * KBF);
     if (kb >= N) continue;  // the last round of a group without a block (the barriers above still meet)
     // S^T = K Q^T
@@ -644,7 +657,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem&
   constexpr int RW = 34 * 64;
   static_assert((KG - 1) * QW * RW * 4 <= F32_LDS, "merge buffer");
   __syncthreads();  // every wave is past its last block
-  if (kg > 0) {
+  if (kg > 0 && kg < KG) {
     float* r = red + ((kg - 1) * QW + qw) * RW;
     r[lane] = m_run;
     r[64 + lane] = l_run;
@@ -707,16 +720,17 @@ __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem&
 }
 
 // One workgroup per work entry and head.  What bounds it at full load is the
-// matrix cores: 6 heads of 10800 tokens take 954 us, 188 TFLOP/s of FP32 work
-// or 1128 TFLOP/s of BF16 products (FP32 MFMAs: 1371 us); 6 heads of 3600
-// tokens, 174 workgroups on 256 CUs, 247 -> 148 us; 6 heads of 576 43.7 ->
-// 21.6 us.  Errors against 64 bits fall from 1.3e-6 to 9.2e-7 relative at 3600
+// matrix cores: 6 heads of 10800 tokens take 916 us, 196 TFLOP/s of FP32 work
+// or 1172 TFLOP/s of BF16 products (FP32 MFMAs: 1371 us); 6 heads of 3600
+// tokens, 174 workgroups on 256 CUs, 247 -> 141 us; 6 heads of 576 43.7 ->
+// 17.3 us, three rounds of a wave's block at 3.3 us, its splits and products
+// one after the other.  Errors against 64 bits fall from 1.3e-6 to 9.2e-7 relative at 3600
 // tokens and from 2.1e-6 to 1.2e-6 at 10800.
 __global__ __launch_bounds__(F32_NT, 2) void attn_f32_kernel(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[F32_LDS];
   AttnItem it;
   if (!attn_item(a, P_FP32, it)) return;
-  if (it.tile == 64) attn_f32_tile<2, 4, 32>(a, it, smem);
+  if (it.tile == 32) attn_f32_tile<1, 6, 32>(a, it, smem);
   else attn_f32_tile<4, 2, 64>(a, it, smem);
 }
 
@@ -1023,7 +1037,8 @@ int launch_attention_one(Prec prec, const void* q, const void* k, const void* vt
   memset(&a, 0, sizeof(a));
   a.q = q; a.k = k; a.vt = vt; a.o = o; a.heads = heads; a.ldqk = ld; a.ldv = ld;
   a.one_n = ntok;
-  a.nwork = cdiv(ntok, attn_tile(prec, ntok));
+  a.tile = attn_tile_all(prec, ntok, heads);
+  a.nwork = cdiv(ntok, a.tile);
   return launch_attention(prec, a, s, exps);
 }
 

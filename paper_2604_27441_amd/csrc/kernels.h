@@ -74,14 +74,17 @@ struct GemmArgs {
 constexpr int ATTN_TARGET_TILE = 0x8000;
 constexpr int ATTN_MAX_OP_HEADS = 64;  // heads of a launch whose E8M0 exponents travel in its arguments
 
-// Queries per work entry of a request of N tokens.  FP32 requests of at most
-// 1024 tokens take 64-query tiles whose waves split the keys four ways: 6
-// heads of 576 tokens are then 54 workgroups of 5 rounds (21.6 us; 30
-// workgroups of 5 twice as long rounds 28.8 us), 1024 tokens 33 us.  The rule
-// looks at the request alone, so that its result is the same in every batch;
-// a launch that fills the GPU whatever its tiles (AttnArgs::tile) does better
-// with 128 (48 heads of 576 tokens 47 against 35 us).
-__host__ __device__ inline int attn_tile(Prec p, int N) { return p == P_FP32 && N <= 1024 ? 64 : 128; }
+// Queries per work entry of a request of N tokens.  FP32 requests take 32-query
+// tiles whose waves split the keys six ways while six heads of them are at most
+// one workgroup per CU (us for 6 heads, 128-query tiles first: 576 tokens 28.8
+// and 17.3, 1024 tokens 45 and 27, 1300 tokens 54 and 33, 1500 tokens 61 and 65).
+// The rule looks at the request alone, so that its result is the same in every
+// batch; launches that know all of their work (AttnArgs::tile) ask whether all
+// their tiles are (24 heads of 576 tokens: 31 and 35).
+__host__ __device__ inline int attn_tile(Prec p, int N) { return p == P_FP32 && N <= 1344 ? 32 : 128; }
+inline int attn_tile_all(Prec p, int N, int heads) {
+  return p == P_FP32 && (long long)heads * cdiv(N, 32) <= 256 ? 32 : 128;
+}
 
 struct AttnArgs {
   const void* q;     // [heads][ldqk rows][64], pre-scaled by log2(e)/sqrt(64)

@@ -495,8 +495,7 @@ int setup(revo_trainer* t, const revo_train_config& c) {
   t->h_reqs.resize(t->B);
   // work lists: query tiles (forward attention), 64-row blocks (backward)
   std::vector<int> wf, wb, rowmap;
-  // (six heads of 128-query tiles that fill most of the CUs: see attn_tile)
-  t->attn_tile_f = t->B * 6 * cdiv(t->N, 128) >= 160 ? 128 : attn_tile(P_FP32, t->N);
+  t->attn_tile_f = attn_tile_all(P_FP32, t->N, 6 * t->B);
   const int tile = t->attn_tile_f;
   for (int r = 0; r < t->B; ++r) {
     for (int q = 0; q * tile < t->N; ++q) wf.push_back((r << 16) | q);

@@ -232,12 +232,12 @@ def test_attention(prec, heads, ntok):
             assert np.sqrt(np.mean(err ** 2)) < 4e-3 * np.sqrt(np.mean(ref ** 2)) + 1e-3
 
 
-# both FP32 tile forms (64 queries and four key groups up to 1024 tokens, 128
-# and two beyond): a last key block and rounds of the key groups that are
-# empty, full or partial, a last query tile of one row
-@pytest.mark.parametrize("ntok", [31, 33, 65, 127, 129, 161, 1024, 1025, 1088, 1153])
-def test_attention_fp32_tiles(ntok):
-    heads = 2
+# both FP32 tile forms (32 queries and six key groups while heads x tiles are at
+# most 256, 128 queries and two groups beyond): a last key block and rounds of
+# the key groups that are empty, full or partial, a last query tile of one row
+@pytest.mark.parametrize("heads,ntok", [(2, 31), (2, 33), (2, 65), (2, 161), (2, 193), (2, 385), (8, 1024), (8, 1025), (9, 1088), (9, 1153),
+                                        (65, 97), (65, 127), (65, 128), (129, 33), (129, 64), (66, 129)])
+def test_attention_fp32_tiles(heads, ntok):
     qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=1.5)
     o = torch.full((ntok + 1, heads * 64), 7.0, dtype=torch.float32).cuda()
     rc = _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None)
@@ -249,13 +249,12 @@ def test_attention_fp32_tiles(ntok):
         assert np.abs(got[:ntok, h * 64:(h + 1) * 64] - ref).max() < 2e-5 * np.abs(v64[h]).max()
 
 
-@pytest.mark.parametrize("ntok", [300, 1100])
-def test_attention_fp32_range(ntok):
+@pytest.mark.parametrize("heads,ntok", [(1, 300), (33, 300)])   # 32- and 128-query tiles
+def test_attention_fp32_range(heads, ntok):
     """FP32 operands over the whole range: a key whose scores are -inf counts
     nothing, an infinite value reaches its dimension alone, and a query whose
     scores hold a NaN (query 40 meets the infinite key with a zero, query 41
     is NaN itself) leaves the other rows as they are."""
-    heads = 1
     qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=1.0)
     q, k, v = q64[0].copy(), k64[0].copy(), v64[0].copy()
     q[:, 5] = np.abs(q[:, 5]) + 0.1
@@ -271,9 +270,9 @@ def test_attention_fp32_range(ntok):
     qd[0, :ntok] = torch.tensor((q * f).astype(np.float32)).cuda()
     kd[0, :ntok] = torch.tensor(k.astype(np.float32)).cuda()
     vt[0, :, :ntok] = torch.tensor(v.astype(np.float32).T.copy()).cuda()
-    o = torch.zeros((ntok, 64), dtype=torch.float32).cuda()
+    o = torch.zeros((ntok, heads * 64), dtype=torch.float32).cuda()
     assert _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None) == 0
-    got = o.double().cpu().numpy()
+    got = o.double().cpu().numpy()[:, :64]
     q32, k32 = (q * f).astype(np.float32).astype(np.float64) / f, k.astype(np.float32).astype(np.float64)
     k32[7, 5] = 0
     rows = (np.arange(ntok) != 40) & (np.arange(ntok) != 41)
@@ -290,13 +289,12 @@ def test_attention_fp32_range(ntok):
     assert np.isposinf(got[rows, 3]).all()
 
 
-@pytest.mark.parametrize("ntok", [300, 1100])
-def test_attention_fp32_large_scores(ntok):
+@pytest.mark.parametrize("heads,ntok", [(1, 300), (33, 300)])   # 32- and 128-query tiles
+def test_attention_fp32_large_scores(heads, ntok):
     """Scores past what the split products hold (query 40: 1e30 at key 21,
     -1e14 and below at the others; query 50: -1e30 everywhere but -1e29 at
     key 200) give the row of the key with the largest score; the other rows
     are ordinary."""
-    heads = 1
     qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=1.0)
     q, k, v = q64[0].copy(), k64[0].copy(), v64[0]
     q[:, 8:10] = 0
@@ -307,9 +305,9 @@ def test_attention_fp32_large_scores(ntok):
     f = math.log2(math.e) / 8
     qd[0, :ntok] = torch.tensor((q * f).astype(np.float32)).cuda()
     kd[0, :ntok] = torch.tensor(k.astype(np.float32)).cuda()
-    o = torch.zeros((ntok, 64), dtype=torch.float32).cuda()
+    o = torch.zeros((ntok, heads * 64), dtype=torch.float32).cuda()
     assert _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None) == 0
-    got = o.double().cpu().numpy()
+    got = o.double().cpu().numpy()[:, :64]
     ref = oracle.attention_head((q * f).astype(np.float32).astype(np.float64) / f, k.astype(np.float32).astype(np.float64), v)
     ref[40], ref[50] = v[21], v[200]
     assert np.abs(got - ref).max() < 2e-5 * np.abs(v).max()
