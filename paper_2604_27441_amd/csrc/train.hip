@@ -509,7 +509,8 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// The tiles are products of 64 x 64 blocks over 64 (head dimension, queries
+// First the FP32-MFMA form of the two passes, for values out of the split
+// products' range: products of 64 x 64 blocks over 64 (head dimension, queries
 // or keys), on FP32 32x32x2 MFMAs: lane l supplies A[l % 32][k] and B[k][l %
 // 32] for k = 2 step + l / 32, and holds C[row(i, l)][l % 32] (acc_row).
 // Each of the 4 waves takes one 32 x 32 tile per product.  The operand a
@@ -552,14 +553,15 @@ __device__ __forceinline__ void store_cols(float (*t)[65], const float (&r)[16])
   for (int j = 0; j < 16; ++j) t[c][db + 4 * j] = r[j];
 }
 
-// dK and dV of one 64-key block of one (request, head), looping over the
-// request's query blocks.  Per block: wave (qc, kt) forms the 32 x 32 piece
-// of S = Qs K^T and dP = dO V^T (K and V rows of its keys in registers), P
-// and dS go through LDS; wave (kt, dt) accumulates dV += P^T dO and
-// dK += dS^T Qs over the block's 64 queries.
-__global__ __launch_bounds__(TB, 2) void attn_bwd_dkdv_kernel(const AttnBwdArgs a) {
-  __shared__ float Qs[64][65], Ds[64][65], Pt[64][65], dSt[64][65];
-  __shared__ float lse_s[64], dv_s[64];
+// dK and dV of one 64-key block on FP32 MFMAs.  Per query block: wave (qc,
+// kt) forms the 32 x 32 piece of S = Qs K^T and dP = dO V^T (K and V rows of
+// its keys in registers), P and dS go through LDS; wave (kt, dt) accumulates
+// dV += P^T dO and dK += dS^T Qs over the block's 64 queries.
+__device__ __forceinline__ void attn_bwd_dkdv_f32(const AttnBwdArgs& a, uint8_t* smem) {
+  float(*Qs)[65] = reinterpret_cast<float(*)[65]>(smem);
+  float(*Ds)[65] = Qs + 64, (*Pt)[65] = Ds + 64, (*dSt)[65] = Pt + 64;
+  float* lse_s = reinterpret_cast<float*>(dSt + 64);
+  float* dv_s = lse_s + 64;
   const int h = blockIdx.y;
   const int w = a.work[blockIdx.x];
   const ReqDesc& d = a.reqs[w >> 16];
@@ -649,12 +651,13 @@ __global__ __launch_bounds__(TB, 2) void attn_bwd_dkdv_kernel(const AttnBwdArgs 
   }
 }
 
-// dQ of one 64-query block of one (request, head), looping over key blocks.
-// Per block: wave (kt, qc) forms S^T = K Qs^T and dP^T = V dO^T (keys as
-// rows; Q and dO rows of its queries in registers), dS^T goes through LDS;
-// wave (dt, qc2) accumulates dQ^T += K^T dS^T.
-__global__ __launch_bounds__(TB, 2) void attn_bwd_dq_kernel(const AttnBwdArgs a) {
-  __shared__ float Ks[64][65], Vs[64][65], dSt[64][65];
+// dQ of one 64-query block on FP32 MFMAs.  Per key block: wave (kt, qc) forms
+// S^T = K Qs^T and dP^T = V dO^T (keys as rows; Q and dO rows of its queries
+// in registers), dS^T goes through LDS; wave (dt, qc2) accumulates dQ^T += K^T
+// dS^T.
+__device__ __forceinline__ void attn_bwd_dq_f32(const AttnBwdArgs& a, uint8_t* smem) {
+  float(*Ks)[65] = reinterpret_cast<float(*)[65]>(smem);
+  float(*Vs)[65] = Ks + 64, (*dSt)[65] = Vs + 64;
   const int h = blockIdx.y;
   const int w = a.work[blockIdx.x];
   const ReqDesc& d = a.reqs[w >> 16];
@@ -726,6 +729,378 @@ __global__ __launch_bounds__(TB, 2) void attn_bwd_dq_kernel(const AttnBwdArgs a)
     float* row = a.dqkv + (size_t)(base + q0 + q) * 3 * D + h * 64 + 32 * dt;
 #pragma unroll
     for (int i = 0; i < 16; ++i) row[acc_row(i, lane)] = gq[i] * 0.125f;
+  }
+}
+
+// The products themselves run on the BF16 matrix cores, on exact three-way
+// splits (common.h split3, times 2^24) and six products per pair, smallest
+// first, as in the forward pass; true values are 2^-48 of the accumulators.
+// A 64 x 64 block is kept as three planes of 64 rows of 128 bytes, 16-byte
+// chunk c of row r at slot c ^ bw_swz(r): conflict-free both for a lane that
+// reads eight consecutive elements of its row and for the transposing reads,
+// which take four rows of 32 bytes in each group of 16 lanes.
+//
+// MFMA-bound: per 64 x 64 block and wave 96 (dK, dV) and 72 (dQ) products of
+// 32 cycles where the FP32 unit takes 128 and 96 of 64.  8 requests of 576
+// tokens: dK and dV 60 -> 36 us at 3 heads, dQ 39 -> 29 (216 workgroups of 9
+// blocks), at 6 heads and beside the weight gradients of the other stream up to
+// 91 -> 72 and 62 -> 55; the whole step at 256 x 192, batch 8, 11.39 -> 10.59 ms.  The
+// operand that a wave keeps (K, or Q and dO) is in registers, V in LDS: with V
+// in registers too there is no room for the next block's rows.
+constexpr int BW_PL = 64 * 128;  // bytes per plane
+constexpr int BW_A[6] = {0, 2, 1, 0, 1, 0}, BW_B[6] = {2, 0, 1, 1, 0, 0};
+
+__device__ __forceinline__ int bw_swz(int row) { return ((row >> 1) & 1) << 2 | ((row >> 2) & 3); }
+
+// 64 x 64 floats of a [rows][pitch] matrix from row r0, column c0: thread t
+// takes 4 columns from 4 (t % 16) of rows t / 16 + 16 j; what lies past the
+// descriptor's range reads as zeros
+__device__ __forceinline__ void bw_fetch(float4 (&r)[4], const __amdgpu_buffer_rsrc_t rs, int pitch, int r0, int c0) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    r[j] = __builtin_bit_cast(
+        float4, __builtin_amdgcn_raw_buffer_load_b128(
+                    rs, ((r0 + (int)(threadIdx.x >> 4) + 16 * j) * pitch + c0 + (int)(threadIdx.x & 15) * 4) * 4, 0, 0));
+}
+__device__ __forceinline__ void bw_land(uint8_t* pl, const float4 (&r)[4]) {
+  const int c = threadIdx.x & 15;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = (threadIdx.x >> 4) + 16 * j;
+    uint2 p[3];
+    split3x4(r[j], p);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *reinterpret_cast<uint2*>(pl + k * BW_PL + row * 128 + (((c >> 1) ^ bw_swz(row)) << 4) + (c & 1) * 8) = p[k];
+  }
+}
+// fragment: eight consecutive elements, from 8 chunk, of this lane's row
+__device__ __forceinline__ bf16x8 bw_row(const uint8_t* pl, int row, int chunk) {
+  return *reinterpret_cast<const bf16x8*>(pl + row * 128 + ((chunk ^ bw_swz(row)) << 4));
+}
+// fragment: column 32 sub + lane % 32 of rows r0 .. r0 + 3 and r1 .. r1 + 3 (both
+// multiples of 4, alike in the lanes of a half)
+__device__ __forceinline__ bf16x8 bw_cols(const uint8_t* pl, int r0, int r1, int sub, int lane) {
+  typedef __attribute__((ext_vector_type(4))) short s4;
+  typedef __attribute__((address_space(3))) s4* lds4;
+  const int sr = (lane & 15) >> 2, chunk = sub * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1), piece = (lane & 1) * 8;
+  s4 v[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int row = (k ? r1 : r0) + sr;
+    v[k] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(pl + row * 128 + ((chunk ^ bw_swz(row)) << 4) + piece));
+  }
+  return __builtin_bit_cast(bf16x8, v);
+}
+__device__ __forceinline__ void bw_mma(f32x16& acc, const bf16x8 (&x)[3], const bf16x8 (&y)[3]) {
+#pragma unroll
+  for (int p = 0; p < 6; ++p) OpBF16::mma(acc, x[BW_A[p]], y[BW_B[p]]);
+}
+// fragments of one row's dimensions 16 c + 8 half .. + 7, c = 0 .. 3, from memory
+__device__ __forceinline__ void bw_row_frags(bf16x8 (&f)[4][3], const __amdgpu_buffer_rsrc_t rs, int off, int half) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    uint2 lo[3], hi[3];
+    const int o = (off + 16 * c + 8 * half) * 4;
+    split3x4(__builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0)), lo);
+    split3x4(__builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16, 0, 0)), hi);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) f[c][j] = __builtin_bit_cast(bf16x8, make_uint4(lo[j].x, lo[j].y, hi[j].x, hi[j].y));
+  }
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t bw_rsrc(const float* p, int elems) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, elems * 4, 0x00020000);
+}
+
+// dK and dV of one 64-key block of one (request, head), looping over the
+// request's query blocks.  Wave (qh, ks) takes 32 queries of each block and 32
+// keys: S = Q K^T and dP = dO V^T with a key per lane, so that P and dS are the
+// second operands of dV^T += dO^T P and dK^T += Q^T dS as they stand (their first
+// operands are transposing reads in the same order of the queries).  The two
+// query halves are added at the end.  Values past 2^80, infinities and NaN
+// leave an accumulator or a score that is not finite: the block is then done
+// again on FP32 MFMAs.
+__global__ __launch_bounds__(TB, 2) void attn_bwd_dkdv_kernel(const AttnBwdArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[9 * BW_PL + 528];
+  static_assert(4 * 64 * 65 * 4 + 512 <= sizeof(smem), "FP32 form");
+  uint8_t *qp = smem, *dp_ = smem + 3 * BW_PL, *vp = smem + 6 * BW_PL;
+  float* lse_s = reinterpret_cast<float*>(smem + 9 * BW_PL);
+  float* dv_s = lse_s + 64;
+  int* flag = reinterpret_cast<int*>(dv_s + 64);
+  const int h = blockIdx.y;
+  const int w = a.work[blockIdx.x];
+  const ReqDesc& d = a.reqs[w >> 16];
+  const int N = d.J * d.P, base = d.tok_off;
+  const int k0 = (w & 0xFFFF) * 64;
+  const int nk = min(64, N - k0);
+  const int dpitch = a.heads * 64;
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qh = wave & 1, ks = wave >> 1;
+  // rows past the request read as zeros
+  const __amdgpu_buffer_rsrc_t qrs = bw_rsrc(a.q + (size_t)h * a.ld * 64, (base + N) * 64);
+  const __amdgpu_buffer_rsrc_t krs = bw_rsrc(a.k + (size_t)h * a.ld * 64, (base + N) * 64);
+  const __amdgpu_buffer_rsrc_t drs = bw_rsrc(a.dout + h * 64, (base + N) * dpitch - h * 64);
+  const __amdgpu_buffer_rsrc_t vrs = bw_rsrc(a.vt + (size_t)h * 64 * a.ld, 64 * a.ld);
+  const float *lse = a.lse + (size_t)h * a.ld + base, *dvg = a.dv + (size_t)h * a.ld + base;
+
+  float4 pq[4], pd[4];
+  float pl = 0.0f, pv = 0.0f;
+  {
+    float4 t[4];
+    bw_fetch(t, vrs, a.ld, 0, base + k0);
+    bw_land(vp, t);
+  }
+  auto fetch = [&](int q0) {
+    bw_fetch(pq, qrs, 64, base + q0, 0);
+    bw_fetch(pd, drs, dpitch, base + q0, 0);
+    if (tid < 64) {
+      pl = q0 + tid < N ? lse[q0 + tid] : 0.0f;
+      pv = q0 + tid < N ? dvg[q0 + tid] : 0.0f;
+    }
+  };
+  fetch(0);
+  bf16x8 kf[4][3];
+  bw_row_frags(kf, krs, (base + k0 + 32 * ks + l32) * 64, half);
+  f32x16 gk[2] = {}, gv[2] = {};
+  float chk = 0.0f;
+  for (int q0 = 0; q0 < N; q0 += 64) {
+    if (q0) __syncthreads();  // the previous block is consumed
+    bw_land(qp, pq);
+    bw_land(dp_, pd);
+    if (tid < 64) {
+      lse_s[tid] = 24.0f - pl;
+      dv_s[tid] = pv;
+    }
+    __syncthreads();
+    if (q0 + 64 < N) fetch(q0 + 64);
+    f32x16 sc = {}, dp = {};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      bf16x8 x[3], y[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) x[j] = bw_row(qp + j * BW_PL, 32 * qh + l32, 2 * c + half);
+      bw_mma(sc, x, kf[c]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        x[j] = bw_row(dp_ + j * BW_PL, 32 * qh + l32, 2 * c + half);
+        y[j] = bw_cols(vp + j * BW_PL, 16 * c + 8 * half, 16 * c + 8 * half + 4, ks, lane);
+      }
+      bw_mma(dp, x, y);
+    }
+    // P and dS times 2^24 (queries past the request meet zero rows of Q and dO;
+    // keys past it have lanes of their own, which are not stored)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      uint32_t pw[3][4], sw[3][4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float p[2], ds[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int i = 8 * g + 2 * e + k, ql = 32 * qh + acc_row(i, lane);
+          chk = fmaf(sc[i], 0.0f, chk);
+          p[k] = __builtin_amdgcn_exp2f(fmaf(sc[i], 0x1p-48f, lse_s[ql]));
+          ds[k] = p[k] * fmaf(dp[i], 0x1p-48f, -dv_s[ql]);
+        }
+        split3(p[0], p[1], pw[0][e], pw[1][e], pw[2][e]);
+        split3(ds[0], ds[1], sw[0][e], sw[1][e], sw[2][e]);
+      }
+      bf16x8 pf[3], sf[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        pf[j] = __builtin_bit_cast(bf16x8, pw[j]);
+        sf[j] = __builtin_bit_cast(bf16x8, sw[j]);
+      }
+      const int r0 = 32 * qh + 16 * g + 4 * half;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        bf16x8 x[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) x[j] = bw_cols(dp_ + j * BW_PL, r0, r0 + 8, t, lane);
+        bw_mma(gv[t], x, pf);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) x[j] = bw_cols(qp + j * BW_PL, r0, r0 + 8, t, lane);
+        bw_mma(gk[t], x, sf);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) chk = fmaf(gk[t][i], 0.0f, fmaf(gv[t][i], 0.0f, chk));
+  const bool bad = __any(32 * ks + l32 < nk && !(chk == 0.0f));
+  __syncthreads();
+  if (lane == 0) flag[wave] = bad;
+  // second query half into LDS, added to the first there, rows out of LDS
+  float* red = reinterpret_cast<float*>(smem) + ks * 64 * 64;        // [register][lane]
+  float* out = reinterpret_cast<float*>(smem) + 2 * 64 * 64;         // [key][dK dims, dV dims]
+  constexpr int OP = 132;
+  static_assert((2 * 64 * 64 + 64 * OP) * 4 <= 9 * BW_PL, "output stage");
+  if (qh)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        red[(t * 16 + i) * 64 + lane] = gk[t][i];
+        red[(32 + t * 16 + i) * 64 + lane] = gv[t][i];
+      }
+  __syncthreads();
+  if (flag[0] | flag[1] | flag[2] | flag[3]) {
+    __syncthreads();  // the flags are read
+    attn_bwd_dkdv_f32(a, smem);
+    return;
+  }
+  if (!qh)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float4 vk, vv;
+        float *ek = &vk.x, *ev = &vv.x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * g + e;
+          // dK in units of log2 e: 1 / log2(e)
+          ek[e] = (gk[t][i] + red[(t * 16 + i) * 64 + lane]) * (0x1p-48f * 0.69314718055994531f);
+          ev[e] = (gv[t][i] + red[(32 + t * 16 + i) * 64 + lane]) * 0x1p-48f;
+        }
+        float* o = out + (32 * ks + l32) * OP + 32 * t + 8 * g + 4 * half;
+        *reinterpret_cast<float4*>(o) = vk;
+        *reinterpret_cast<float4*>(o + 64) = vv;
+      }
+  __syncthreads();
+  const int D = a.heads * 64;
+  for (int i = tid; i < nk * 32; i += TB) {
+    const int key = i >> 5, c = (i & 31) * 4;
+    float* row = a.dqkv + (size_t)(base + k0 + key) * 3 * D + D + h * 64;
+    *reinterpret_cast<float4*>(row + (c < 64 ? c : D + c - 64)) = *reinterpret_cast<const float4*>(out + key * OP + c);
+  }
+}
+
+// dQ of one 64-query block of one (request, head), looping over key blocks:
+// the same with the sides exchanged.  Wave (kh, qs) takes 32 keys of each
+// block and 32 queries, S^T = K Q^T and dP^T = V dO^T have a query per lane, and
+// dQ^T += K^T dS^T.
+__global__ __launch_bounds__(TB, 2) void attn_bwd_dq_kernel(const AttnBwdArgs a) {
+  constexpr int SM = 3 * 64 * 65 * 4 > 6 * BW_PL ? 3 * 64 * 65 * 4 : 6 * BW_PL;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[SM + 16];
+  uint8_t *kp = smem, *vp = smem + 3 * BW_PL;
+  int* flag = reinterpret_cast<int*>(smem + SM);
+  const int h = blockIdx.y;
+  const int w = a.work[blockIdx.x];
+  const ReqDesc& d = a.reqs[w >> 16];
+  const int N = d.J * d.P, base = d.tok_off;
+  const int q0 = (w & 0xFFFF) * 64;
+  const int nq = min(64, N - q0);
+  const int dpitch = a.heads * 64;
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh = wave & 1, qs = wave >> 1;
+  const int ql = 32 * qs + l32;
+  const __amdgpu_buffer_rsrc_t qrs = bw_rsrc(a.q + (size_t)h * a.ld * 64, (base + N) * 64);
+  const __amdgpu_buffer_rsrc_t krs = bw_rsrc(a.k + (size_t)h * a.ld * 64, (base + N) * 64);
+  const __amdgpu_buffer_rsrc_t drs = bw_rsrc(a.dout + h * 64, (base + N) * dpitch - h * 64);
+  const __amdgpu_buffer_rsrc_t vrs = bw_rsrc(a.vt + (size_t)h * 64 * a.ld, 64 * a.ld);
+
+  float4 pk[4], pv[4];
+  bw_fetch(pk, krs, 64, base, 0);
+  bw_fetch(pv, vrs, a.ld, 0, base);
+  bf16x8 qf[4][3], df[4][3];
+  bw_row_frags(qf, qrs, (base + q0 + ql) * 64, half);
+  bw_row_frags(df, drs, (base + q0 + ql) * dpitch, half);
+  const float lse = 24.0f - (ql < nq ? a.lse[(size_t)h * a.ld + base + q0 + ql] : 0.0f);
+  const float dvq = ql < nq ? a.dv[(size_t)h * a.ld + base + q0 + ql] : 0.0f;
+  f32x16 gq[2] = {};
+  float chk = 0.0f;
+  for (int k0 = 0; k0 < N; k0 += 64) {
+    if (k0) __syncthreads();  // the previous block is consumed
+    bw_land(kp, pk);
+    bw_land(vp, pv);
+    __syncthreads();
+    if (k0 + 64 < N) {
+      bw_fetch(pk, krs, 64, base + k0 + 64, 0);
+      bw_fetch(pv, vrs, a.ld, 0, base + k0 + 64);
+    }
+    f32x16 sc = {}, dp = {};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      bf16x8 x[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) x[j] = bw_row(kp + j * BW_PL, 32 * kh + l32, 2 * c + half);
+      bw_mma(sc, x, qf[c]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) x[j] = bw_cols(vp + j * BW_PL, 16 * c + 8 * half, 16 * c + 8 * half + 4, kh, lane);
+      bw_mma(dp, x, df[c]);
+    }
+    float ds[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      chk = fmaf(sc[i], 0.0f, chk);
+      ds[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], 0x1p-48f, lse)) * fmaf(dp[i], 0x1p-48f, -dvq);
+    }
+    if (k0 + 64 > N)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (k0 + 32 * kh + acc_row(i, lane) >= N) ds[i] = 0.0f;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      uint32_t sw[3][4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split3(ds[8 * g + 2 * e], ds[8 * g + 2 * e + 1], sw[0][e], sw[1][e], sw[2][e]);
+      bf16x8 sf[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) sf[j] = __builtin_bit_cast(bf16x8, sw[j]);
+      const int r0 = 32 * kh + 16 * g + 4 * half;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        bf16x8 x[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) x[j] = bw_cols(kp + j * BW_PL, r0, r0 + 8, t, lane);
+        bw_mma(gq[t], x, sf);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) chk = fmaf(gq[t][i], 0.0f, chk);
+  const bool bad = __any(ql < nq && !(chk == 0.0f));
+  __syncthreads();
+  if (lane == 0) flag[wave] = bad;
+  float* red = reinterpret_cast<float*>(smem) + qs * 32 * 64;  // [register][lane]
+  float* out = reinterpret_cast<float*>(smem) + 2 * 32 * 64;   // [query][dims]
+  constexpr int OP = 68;
+  static_assert((2 * 32 * 64 + 64 * OP) * 4 <= SM, "output stage");
+  if (kh)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) red[(t * 16 + i) * 64 + lane] = gq[t][i];
+  __syncthreads();
+  if (flag[0] | flag[1] | flag[2] | flag[3]) {
+    __syncthreads();  // the flags are read
+    attn_bwd_dq_f32(a, smem);
+    return;
+  }
+  if (!kh)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float4 v;
+        float* ev = &v.x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          ev[e] = (gq[t][4 * g + e] + red[(t * 16 + 4 * g + e) * 64 + lane]) * (0x1p-48f * 0.125f);
+        *reinterpret_cast<float4*>(out + ql * OP + 32 * t + 8 * g + 4 * half) = v;
+      }
+  __syncthreads();
+  const int D = a.heads * 64;
+  for (int i = tid; i < nq * 16; i += TB) {
+    const int q = i >> 4, c = (i & 15) * 4;
+    *reinterpret_cast<float4*>(a.dqkv + (size_t)(base + q0 + q) * 3 * D + h * 64 + c) =
+        *reinterpret_cast<const float4*>(out + q * OP + c);
   }
 }
 

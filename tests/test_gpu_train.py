@@ -164,6 +164,39 @@ def test_tubelet_variants_match_the_oracle(C, k, T):
     _check_update(new, ref["params"], ref["grad"], ot.ADAM_LR)
 
 
+@pytest.mark.parametrize("h,w,scale", [(48, 112, 0), (32, 176, 0), (48, 688, 0), (128, 128, 0), (32, 176, 100)])
+def test_attention_backward_block_edges(h, w, scale):
+    """63, 66, 387 and 192 tokens per request: the attention backward's 64-row
+    blocks with a last one of 63, 2, 3 and 64.  scale: keys times 2^100 and
+    queries over it leave every score alone and take the split products out of
+    their range, so that the FP32-MFMA form does the blocks.  The Q, K and V
+    rows of the weight gradients are held to their own maxima, which can be a
+    few times below the whole tensor's: 1e-4 where the tensor is held to 2e-5."""
+    from paper_2604_27441_amd import Trainer
+    arch = oracle.Arch(channels=3, **TINY)
+    blob = synth.make_weights(5, perturb_seed=6, **TINY)[0].copy()
+    index = {k: v.astype(np.int64) for k, v in
+             oracle.unpack_weights(np.arange(blob.size, dtype=np.float64), arch).items()}
+    for name in ("enc0.qkv.w", "enc0.qkv.b"):
+        blob[index[name][:384]] *= 2.0 ** -scale
+        blob[index[name][384:768]] *= 2.0 ** scale
+    samples = synth.make_pretrain_batch(7, 2, h, w, 3)
+    ref = ot.train_step(blob, samples, arch)
+    with Trainer(blob, 3, 2, h, w, **TINY) as tr:
+        loss = tr.step(*_dev(samples, 3))
+        grad = tr.grads()
+    assert abs(loss - ref["loss"]) <= 1e-5 * abs(ref["loss"])
+    _check_grads(grad, ref["grad"], arch, rtol=2e-5)
+    for name in (n for n in index if n.endswith("qkv.w")):
+        rows = index[name].shape[0] // 3
+        for part in range(3):
+            i = index[name][part * rows:(part + 1) * rows].ravel()
+            want = ref["grad"][i]
+            err = np.abs(grad[i].astype(np.float64) - want).max() / np.abs(want).max()
+            print(f"{name} {'QKV'[part]}: {err:.2g}")
+            assert err <= 1e-4, (name, part, err)
+
+
 def test_batch_gradient_is_the_mean_of_its_halves():
     """At batch 16 (9216 token rows, past what the oracle can check in a
     test), the loss is the batch mean, so the step's loss and gradient equal
