@@ -1203,8 +1203,15 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
     return -22;  // not reached: every BF16 dense product takes the ring
   } else {
     if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4) {
-      // Four tile forms, by how many tiles they give the 256 CUs (us on one
+      // Five tile forms, by how many tiles they give the 256 CUs (us on one
       // box for M x N x K, with the FP32-MFMA kernel these replace first):
+      //  32 x 32, 4 waves in 4 k groups, while its tiles are at most one per CU
+      //   (latency: a workgroup reads a third less than a 64 x 32 one, and two
+      //   networks' workgroups fit one CU: 576 x 384 x 1536 54.0 -> 14.8, 64 x 32
+      //   17.8; 576 x 384 x 384 5.8, 6.7; the 256 x 192 recovery of two networks
+      //   1388 -> 1328; 800 x 384 x 1536, 300 tiles, 20.0 against 18.3 with the
+      //   next form; 8 waves in 8 k groups with 96 KB of LDS 12.6 alone, but the
+      //   recovery 1296 where this one takes 1277);
       //  64 x 32, 8 waves in 4 k groups, while its tiles are at most one per
       //   CU (latency: 576 x 384 x 1536 54.0 -> 18.6; 64 x 64 26.3);
       //  128 x 64, 8 waves in 2 k groups, from 160 to 256 tiles, about one per
@@ -1217,7 +1224,10 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
       const long long gm64 = cdiv(a.M, 64);
       const long long t6432 = gm64 * (a.N / 32), t6464 = gm64 * (a.N / 64), t12864 = (long long)gm * (a.N / 64);
       const long long t128 = a.N % 128 == 0 ? (long long)gm * (a.N / 128) : 0;
-      if (t6432 <= 256 && a.K % 64 == 0)
+      const long long t3232 = (long long)cdiv(a.M, 32) * (a.N / 32);
+      if (t3232 <= 256 && a.K % 64 == 0)
+        gemm_f32_kernel<32, 32, 1, 1, 4, 64, 2, EPI><<<(unsigned)t3232, 256, 0, s>>>(a);
+      else if (t6432 <= 256 && a.K % 64 == 0)
         gemm_f32_kernel<64, 32, 2, 1, 4, 64, 2, EPI><<<(unsigned)t6432, 512, 0, s>>>(a);
       else if (t6464 <= 700 && !(t12864 >= 160 && t12864 <= 256))
         gemm_f32_kernel<64, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t6464, 512, 0, s>>>(a);

@@ -63,10 +63,10 @@ def test_linear(prec, M, N, K, epi):
     assert np.all(np.abs(got - ref) <= tol + 1e-7), float(np.abs(got - ref).max())
 
 
-# One shape on each side of the lines between the FP32 tile forms (64 x 32,
-# 64 x 64, 128 x 64 and 128 x 128), K of an odd number of 32-value stages
-# (which the 64-value stages of the 64 x 32 form do not take), ragged rows
-@pytest.mark.parametrize("M,N,K", [(63, 64, 96), (65, 64, 64), (1365, 384, 192), (1366, 384, 192), (1344, 384, 96), (3393, 384, 32),
+# One shape on each side of the lines between the FP32 tile forms (32 x 32,
+# 64 x 32, 64 x 64, 128 x 64 and 128 x 128), K of an odd number of 32-value stages
+# (which the 64-value stages of the first two forms do not take), ragged rows
+@pytest.mark.parametrize("M,N,K", [(63, 64, 96), (1, 64, 64), (65, 64, 64), (672, 384, 1536), (673, 384, 192), (1365, 384, 192), (1366, 384, 192), (1344, 384, 96), (3393, 384, 32),
                                    (7460, 384, 64), (3968, 1536, 64), (4097, 1536, 160), (20001, 64, 64)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
 def test_linear_fp32_tile_forms(M, N, K, epi):
@@ -90,8 +90,8 @@ def test_linear_fp32_tile_forms(M, N, K, epi):
     assert np.abs(out.double().cpu().numpy() - ref).max() <= tol
 
 
-# one shape per FP32 tile form (64 x 32, 64 x 64, 128 x 64, 128 x 128)
-@pytest.mark.parametrize("M,N,K", [(100, 64, 128), (2300, 576, 64), (3000, 512, 64), (6200, 1024, 64)])
+# one shape per FP32 tile form (32 x 32, 64 x 32, 64 x 64, 128 x 64, 128 x 128)
+@pytest.mark.parametrize("M,N,K", [(100, 64, 128), (1000, 384, 128), (2300, 576, 64), (3000, 512, 64), (6200, 1024, 64)])
 def test_linear_fp32_range(M, N, K):
     """FP32 operands over the whole range: infinities, NaNs and the largest
     values give what IEEE products and sums give, and rows of tiny and
