@@ -101,6 +101,9 @@ struct revo_trainer {
   float *dH1 = nullptr, *da = nullptr, *dO = nullptr, *dqkv = nullptr;
   float *part = nullptr, *dvec = nullptr, *splitk = nullptr;
   size_t splitk_elems = 0;
+  ColSum* d_lnsum = nullptr;  // the LayerNorm gradients' column sums of a step
+  int nlnsum = 0;
+  size_t ln_stride = 0;  // floats of one LayerNorm's partials in lnpart
   TrDesc* d_tr = nullptr;  // the weight transposes of a step
   // the weight gradients run on s2 beside the input-gradient chain on s:
   // ev_fork orders s2 after s, ev_p1 / ev_p2 mark a block's first and
@@ -211,13 +214,13 @@ int input_grad(revo_trainer* t, const float* dy, const Lin& l, float* dx, int Mr
   return mm(t, dy, t->wT + l.w, dx, Mrows, l.in, l.out, l.in);
 }
 
-// LayerNorm backward of rows [0, rows): adds dL/dx into dres, writes the
-// gain and shift gradients
-int ln_grad(revo_trainer* t, const float* x, size_t g_off, size_t b_off, const float* dy, const float* din, float* dout,
+// LayerNorm backward of rows [0, rows): adds dL/dx into dres and leaves the
+// partial sums of its gain and shift gradients in its own slot of lnpart
+// (block i's LN2 and LN1: slots 2i and 2i + 1, then LN_dec and LN_enc)
+int ln_grad(revo_trainer* t, int slot, const float* x, size_t g_off, const float* dy, const float* din, float* dout,
             int rows, int D, const int* rowmap) {
-  if (b_off != g_off + (size_t)D) return -22;  // one sum writes both vectors
-  return launch_ln_bwd(x, t->theta + g_off, dy, din, dout, t->lnpart, t->ln_blocks, rows, D, rowmap, t->grad + g_off,
-                       t->s);
+  return launch_ln_bwd(x, t->theta + g_off, dy, din, dout, t->lnpart + slot * t->ln_stride, t->ln_blocks, rows, D,
+                       rowmap, t->s);
 }
 
 // s2 continues after everything enqueued on s so far
@@ -276,7 +279,7 @@ int block_fwd(revo_trainer* t, const BlockL& b, BlockAct& A, float* xout, int D,
 // s waits for the first before it rewrites dx, and for the previous block's
 // second before it rewrites dmid and dqkv.  dH1 is rewritten only after
 // the previous block's first pair, which s waited for at that block's end.
-int block_bwd(revo_trainer* t, const BlockL& b, const BlockAct& A, float* dx, int D, int heads) {
+int block_bwd(revo_trainer* t, int i, const BlockL& b, const BlockAct& A, float* dx, int D, int heads) {
   int e;
   hipStream_t s = t->s;
   const int M = t->Mpad;
@@ -294,7 +297,7 @@ int block_bwd(revo_trainer* t, const BlockL& b, const BlockAct& A, float* dx, in
     return e;
   if ((e = input_grad(t, t->dH1, b.fc1, t->da, M))) return e;  // da2 = dH1 W1
   if ((e = wait_wgrad(t, t->ev_p2))) return e;                  // the previous block's dmid and dqkv readers
-  if ((e = ln_grad(t, A.xmid, b.ln2g, b.ln2b, t->da, dx, t->dmid, M, D, nullptr))) return e;  // d(xmid)
+  if ((e = ln_grad(t, 2 * i, A.xmid, b.ln2g, t->da, dx, t->dmid, M, D, nullptr))) return e;  // d(xmid)
   // xmid = xin + Proj(Attn(LN1(xin)))
   if ((e = input_grad(t, t->dmid, b.proj, t->dO, M))) return e;
   // the attention backward writes the rows of the batch's tokens only; the
@@ -310,7 +313,7 @@ int block_bwd(revo_trainer* t, const BlockL& b, const BlockAct& A, float* dx, in
       (e = mark_wgrad(t, t->ev_p2)))
     return e;
   if ((e = wait_wgrad(t, t->ev_p1))) return e;  // the first pair has read dx
-  return ln_grad(t, A.xin, b.ln1g, b.ln1b, t->da, t->dmid, dx, M, D, nullptr);
+  return ln_grad(t, 2 * i + 1, A.xin, b.ln1g, t->da, t->dmid, dx, M, D, nullptr);
 }
 
 // the transposed weights the dX products read (every layer but the
@@ -341,6 +344,27 @@ int plan_transposes(revo_trainer* t) {
   if (int e = alloc_n(t, &t->d_tr, d.size())) return e;
   // on the trainer's stream, after the allocation's clearing; d is local
   if (hipMemcpyAsync(t->d_tr, d.data(), d.size() * sizeof(TrDesc), hipMemcpyHostToDevice, t->s) != hipSuccess)
+    return REVO_EDEVICE;
+  return hipStreamSynchronize(t->s) == hipSuccess ? 0 : REVO_EDEVICE;
+}
+
+// the sums of every LayerNorm's partials (the slots of ln_grad)
+int plan_ln_sums(revo_trainer* t) {
+  std::vector<ColSum> d;
+  bool pairs = true;  // one sum writes the gain and, right after it, the shift
+  auto add = [&](size_t g, size_t b, int rows, int D) {
+    pairs &= b == g + (size_t)D;
+    d.push_back({t->lnpart + d.size() * t->ln_stride, t->grad + g, ln_bwd_blocks(rows), 2 * D});
+  };
+  for (const BlockL& b : t->L.enc) { add(b.ln2g, b.ln2b, t->Mpad, 384); add(b.ln1g, b.ln1b, t->Mpad, 384); }
+  for (const BlockL& b : t->L.dec) { add(b.ln2g, b.ln2b, t->Mpad, 192); add(b.ln1g, b.ln1b, t->Mpad, 192); }
+  add(t->L.decg, t->L.decb, t->Mh, 192);
+  add(t->L.encg, t->L.encb, t->Mpad, 384);
+  if (!pairs) return -22;
+  t->nlnsum = (int)d.size();
+  if (int e = alloc_n(t, &t->d_lnsum, d.size())) return e;
+  // on the trainer's stream, after the allocation's clearing; d is local
+  if (hipMemcpyAsync(t->d_lnsum, d.data(), d.size() * sizeof(ColSum), hipMemcpyHostToDevice, t->s) != hipSuccess)
     return REVO_EDEVICE;
   return hipStreamSynchronize(t->s) == hipSuccess ? 0 : REVO_EDEVICE;
 }
@@ -433,18 +457,19 @@ int run_step(revo_trainer* t, const revo_train_batch* bt, double* loss_out) {
   hs.w = t->L.head.w + slot * Dd; hs.b = t->L.head.b + slot;
   if ((e = fork_wgrad(t)) || (e = weight_grad(t, t->dhead, t->ahead, t->Mh_pad, hs, t->grad))) return e;
   if ((e = input_grad(t, t->dhead, hs, t->dahead, t->Mh_pad))) return e;
-  if ((e = ln_grad(t, t->zd, t->L.decg, t->L.decb, t->dahead, t->dz, t->dz, t->Mh, Dd, t->d_rowmap))) return e;
+  if ((e = ln_grad(t, 2 * (t->ne + t->nd), t->zd, t->L.decg, t->dahead, t->dz, t->dz, t->Mh, Dd, t->d_rowmap))) return e;
   for (int i = t->nd - 1; i >= 0; --i)
-    if ((e = block_bwd(t, t->L.dec[i], t->act[t->ne + i], t->dz, Dd, 3))) return e;
+    if ((e = block_bwd(t, t->ne + i, t->L.dec[i], t->act[t->ne + i], t->dz, Dd, 3))) return e;
   // z0 = LN_enc(h) W_e2d^T + b + PE
   if ((e = fork_wgrad(t)) || (e = weight_grad(t, t->dz, t->ae, t->Mpad, t->L.e2d, t->grad))) return e;
   if ((e = input_grad(t, t->dz, t->L.e2d, t->da, t->Mpad))) return e;
   if (hipMemsetAsync(t->dxe, 0, (size_t)t->Mpad * De * 4, s) != hipSuccess) return REVO_EDEVICE;
-  if ((e = ln_grad(t, t->xe, t->L.encg, t->L.encb, t->da, t->dxe, t->dxe, t->Mpad, De, nullptr))) return e;
+  if ((e = ln_grad(t, 2 * (t->ne + t->nd) + 1, t->xe, t->L.encg, t->da, t->dxe, t->dxe, t->Mpad, De, nullptr))) return e;
   for (int i = t->ne - 1; i >= 0; --i)
-    if ((e = block_bwd(t, t->L.enc[i], t->act[i], t->dxe, De, 6))) return e;
+    if ((e = block_bwd(t, i, t->L.enc[i], t->act[i], t->dxe, De, 6))) return e;
   // h0 = U W_emb^T + b + PE
   if ((e = fork_wgrad(t)) || (e = weight_grad(t, t->dxe, t->U, t->Mpad, t->L.emb, t->grad))) return e;
+  if ((e = launch_colsum_batch(t->d_lnsum, t->nlnsum, 2 * De, s))) return e;
   // every dW launch is done before Adam reads the gradients
   if ((e = mark_wgrad(t, t->ev_join)) || (e = wait_wgrad(t, t->ev_join))) return e;
 
@@ -530,10 +555,11 @@ int setup(revo_trainer* t, const revo_train_config& c) {
   }
   const size_t Mx = Mp > (size_t)t->Mh_pad ? Mp : (size_t)t->Mh_pad;
   t->ln_blocks = ln_bwd_blocks((int)Mx);
+  t->ln_stride = (size_t)t->ln_blocks * 2 * De;
   const size_t widest = (size_t)(t->Lt > 4 * De ? t->Lt : 4 * De);
   if ((e = alloc_n(t, &t->dpred, (size_t)t->B * t->H * t->W * t->C)) ||
       (e = alloc_n(t, &t->dhead, (size_t)t->Mh_pad * 256 * t->C)) || (e = alloc_n(t, &t->dahead, (size_t)t->Mh_pad * Dd)) ||
-      (e = alloc_n(t, &t->lnpart, (size_t)t->ln_blocks * 2 * 512)) || (e = alloc_n(t, &t->dxe, Mp * De)) || (e = alloc_n(t, &t->dz, Mp * Dd)) ||
+      (e = alloc_n(t, &t->lnpart, (2 * (t->ne + t->nd) + 2) * t->ln_stride)) || (e = alloc_n(t, &t->dxe, Mp * De)) || (e = alloc_n(t, &t->dz, Mp * Dd)) ||
       (e = alloc_n(t, &t->dH1, Mp * 4 * De)) || (e = alloc_n(t, &t->da, Mp * De)) || (e = alloc_n(t, &t->dmid, Mp * De)) ||
       (e = alloc_n(t, &t->dO, Mp * De)) || (e = alloc_n(t, &t->dqkv, Mp * 3 * De)) ||
       (e = alloc_n(t, &t->part, (size_t)t->max_chunks * widest)) || (e = alloc_n(t, &t->dvec, (size_t)6 * t->ld)) ||
@@ -543,7 +569,7 @@ int setup(revo_trainer* t, const revo_train_config& c) {
   t->splitk_elems = (size_t)512 * 128 * 128 + (size_t)64 * 1536 * 64;
   if ((e = alloc_n(t, &t->splitk, t->splitk_elems))) return e;
   t->h_loss_part.assign(t->loss_blocks, 0.0);
-  if ((e = plan_transposes(t))) return e;
+  if ((e = plan_transposes(t)) || (e = plan_ln_sums(t))) return e;
   return hipStreamSynchronize(t->s) == hipSuccess ? 0 : REVO_EDEVICE;
 }
 
