@@ -457,11 +457,20 @@ int forward(const ModelW& m, Workspace& w, int slot, int nrec, int nall, int com
     const int capW = capM / min_attn_tile(m.prec) + w.max_req;
     const int capPix = 4096 * 4096;
     hipGraph_t g = nullptr;
-    REVO_HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
     const int capWn = capW < w.max_work ? capW : w.max_work;
-    int rc = enqueue_net(m, w, capM, capM, capWn, capWn, w.max_req, w.max_req, capPix, composite, true, 0.0, 0.0, 0.0,
-                         0.0, false, s);
-    hipError_t e = hipStreamEndCapture(s, &g);
+    // Captured on a stream of its own: the completion thread may wait at the
+    // same time for an event last recorded on s (the batch before), which fails
+    // and invalidates a capture of s.
+    hipStream_t cs = nullptr;
+    REVO_HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+    int rc = -5;
+    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
+    if (e == hipSuccess) {
+      rc = enqueue_net(m, w, capM, capM, capWn, capWn, w.max_req, w.max_req, capPix, composite, true, 0.0, 0.0, 0.0,
+                       0.0, false, cs);
+      e = hipStreamEndCapture(cs, &g);
+    }
+    (void)hipStreamDestroy(cs);
     if (rc) {
       if (g) (void)hipGraphDestroy(g);
       return rc;
