@@ -51,7 +51,7 @@ enum revo_status {
 };
 
 enum revo_precision {
-  REVO_FP32 = 0,  /* FP32 operands, FP32 MFMA */
+  REVO_FP32 = 0,  /* FP32 operands and accumulation */
   REVO_BF16 = 1,  /* BF16 operands, FP32 accumulation, FP32 residual/LN/softmax/composite */
   REVO_FP8 = 2    /* OCP FP8 E4M3 operands for the block products (qkv, proj, fc1, fc2) and the
                      encoder-to-decoder projection, with per-output-row weight scales and

@@ -8,9 +8,10 @@
 // its B operand, so each lane ends up owning one token and runs of four
 // consecutive output features: epilogue stores are 8/16-byte row segments.
 //
-// Tile: 128 tokens x BN features x one K stage (128 bytes per operand row;
-// 64 for FP8), 4 waves in a 2 x 2 grid, LDS double-buffered, row pitch padded
-// by 16 bytes.
+// Three kernels: gemm_dma_kernel (dense BF16 and FP8 products), gemm_f32_kernel
+// (dense FP32 products) and gemm_kernel (the rest: 128 tokens x BN features x one
+// K stage of 128 bytes per operand row, 64 for FP8, 4 waves in a 2 x 2 grid, LDS
+// double-buffered, row pitch padded by 16 bytes).
 #include <type_traits>
 
 #include "kernels.h"
@@ -1170,7 +1171,7 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   //   576 x 384 x 1536 18.0 -> 8.4; 3600 x 1152 x 384, 1026 tiles, 9.0 against 8.4
   //   with the next form);
   //  BF16: 128 x 128 on 8 waves of 64 x 32, four waves per SIMD (43200 x 1536 x
-  //   384 GELU 84 -> 82, 3600 x 1152 x 384 8.8 -> 8.4, 10800 x 384 x 1536 25.2 ->
+  //   384 GELU 84 -> 82, now 75, 3600 x 1152 x 384 8.8 -> 8.4, 10800 x 384 x 1536 25.2 ->
   //   23.2), but 4 waves of 64 x 64 for the residual epilogue beyond two
   //   workgroups per CU (43200 x 384 x 384 34.5, 40 on 8 waves);
   //  FP8, whose stages hold twice the K: 128 x 64 on 4 waves, three workgroups

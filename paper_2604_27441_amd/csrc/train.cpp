@@ -5,9 +5,9 @@
 // as inference (tubelet packing, GEMM epilogues with bias / positional
 // embedding / Q-K-V split, attention, LayerNorm, head unpatchify); the
 // backward pass adds transposes, column sums, LayerNorm, GELU and attention
-// backward kernels (train.hip).  Every product of the backward pass is an
-// FP32 MFMA GEMM: dX = dY W runs on the transposed weights, dW = dY^T X on
-// transposed activations.
+// backward kernels (train.hip).  dX = dY W runs on the transposed weights, dW =
+// dY^T X reads both operands as they lie; every product has FP32 operands and
+// accumulation, on exact BF16 splits (gemm.hip gemm_f32_kernel).
 #include <string.h>
 
 #include <cmath>
