@@ -64,14 +64,18 @@ __device__ __forceinline__ bool project_point(const float4& p, unsigned n, const
 // Splat of one tile of SW x SH source points, grid (tiles across, tiles down,
 // frames).  What bounds it is the rate of atomics on the z-buffer's lines: 64
 // neighbouring points land on pieces of some 30 lines, and one atomic per
-// point took 60 us for four 1280x720 frames (61 G atomics/s; this form 34, of
-// which the z-buffer's atomics are 19 and plain stores in their place would be
-// 11).  The tile's target pixels mostly fill a small box, so its points first meet in a z-buffer
-// of that box in LDS, and the box's winners then go to the z-buffer row by row,
-// whole lines per wave.  Tiles whose box does not fit (a strong rotation, a
-// depth edge) send every point to the z-buffer itself.  The minimum is the same
-// either way.
-constexpr int SW = 64, SH = 16, SPT = SW * SH / RT, SBOX = 4096;
+// point took 60 us for four 1280x720 frames (61 G atomics/s; this form 31).  The
+// tile's target pixels mostly fill a small box, so its points first meet in a
+// z-buffer of that box in LDS, and the box's winners then go to the z-buffer row
+// by row, whole lines per wave.  A box that does not fit (a depth edge, noise in
+// the depth, a strong rotation) is cut to the columns around its points' mean,
+// and the other points, or all of a box too tall for that, go to the z-buffer
+// themselves.  The minimum is the same either way.  16 KB of LDS, so that
+// occupancy is 8 workgroups: unprojection and view of four smooth frames 91 us
+// with an atomic per point, 66 with 32 KB and no cut, 62 as it is (buffers in
+// cache; 98.8, 73.4 and 69.9 out of it), a fifth of the depth noise 94, 70.5, 68;
+// frames with much of the depth missing, whose atomics are few, 59, 64.5, 61.
+constexpr int SW = 64, SH = 16, SPT = SW * SH / RT, SBOX = 2048;
 __global__ __launch_bounds__(RT) void splat_kernel(const float4* __restrict__ pts, int H, int W, Pose P, Intr k,
                                                    int Ho, int Wo, unsigned long long* __restrict__ zbuf) {
   __shared__ unsigned long long box[SBOX];
@@ -125,12 +129,49 @@ __global__ __launch_bounds__(RT) void splat_kernel(const float4* __restrict__ pt
   if (u1 < u0) return;  // nothing to render
   // rows of the box start at a multiple of 8 pixels, one 64-byte line
   u0 &= ~7;
-  const int bw = u1 - u0 + 1, bh = v1 - v0 + 1;
+  int bw = u1 - u0 + 1;
+  const int bh = v1 - v0 + 1;
   if ((long long)bw * bh > SBOX) {
+    // the columns around the points' mean that fit, the other points by themselves
+    const bool some = bh <= SBOX / 64;
+    if (some) {
+      __syncthreads();  // ext is read
+      float su = 0.0f;
+      int nu = 0;
+#pragma unroll
+      for (int i = 0; i < SPT; ++i)
+        if (ok[i]) {
+          su += (float)(iu[i] - u0);
+          ++nu;
+        }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        su += __shfl_xor(su, o);
+        nu += __shfl_xor(nu, o);
+      }
+      if (lane == 0) {
+        ext[0][wave] = __float_as_int(su);
+        ext[1][wave] = nu;
+      }
+      __syncthreads();
+      su = 0.0f;
+      nu = 0;
+#pragma unroll
+      for (int w = 0; w < RT / 64; ++w) {
+        su += __int_as_float(ext[0][w]);
+        nu += ext[1][w];
+      }
+      const int width = (SBOX / bh) & ~7;
+      u0 += max(0, min((int)(su / (float)nu) - width / 2, bw - width)) & ~7;
+      bw = min(width, u1 - u0 + 1);
+    }
 #pragma unroll
     for (int i = 0; i < SPT; ++i)
-      if (ok[i]) atomicMin(dst + (long long)iv[i] * Wo + iu[i], key[i]);
-    return;
+      if (ok[i] && (!some || (unsigned)(iu[i] - u0) >= (unsigned)bw)) {
+        atomicMin(dst + (long long)iv[i] * Wo + iu[i], key[i]);
+        ok[i] = false;
+      }
+    if (!some) return;
   }
   const int n = bw * bh;
   for (int i = tid; i < n; i += RT) box[i] = ~0ull;

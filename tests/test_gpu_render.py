@@ -138,13 +138,14 @@ def test_moved_view_small(yaw, pitch, t):
     _check_moved_view(depth, rgb, _pose(yaw, pitch, t), intr, 96, 128)
 
 
-@pytest.mark.parametrize("zoom", [4.0, 1.0, 0.5])
+@pytest.mark.parametrize("zoom", [4.0, 2.0, 1.0, 0.5])
 @pytest.mark.parametrize("H,W", [(17, 65), (35, 130)])
 def test_zoomed_view(zoom, H, W):
     """A view through intrinsics scaled by `zoom`, pixel centres well inside
     their targets, so the winners are exact: at 4 the target boxes of whole
-    source tiles (64 x 16) exceed the LDS z-buffer and points go to the
-    z-buffer one by one, at 0.5 four points meet on a target."""
+    source tiles (64 x 16) are too tall for the LDS z-buffer and points go to
+    the z-buffer one by one, at 2 only the boxes' middle columns fit, at 0.5 four
+    points meet on a target."""
     B = 2
     depth = RNG.integers(500, 3000, (B, H, W)).astype(np.uint16)
     depth[:, ::5, ::3] = 0
