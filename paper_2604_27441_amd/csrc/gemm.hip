@@ -1165,7 +1165,7 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   if ((long long)gm * BM * a.K * esz >= (1LL << 31) || (long long)a.N * a.K * esz >= (1LL << 31)) return -22;
   // Dense BF16 products (all but the head) and FP8 products whose K is a
   // multiple of 128 take the LDS-ring kernel, two stages.  Its tile forms give
-  // the same results bit for bit; which is chosen (us on one box, M x N x K):
+  // the same results bit for bit; which is chosen (us on one card, M x N x K):
   //  64 x 64 on 4 waves while 128-wide tiles would leave most CUs with one
   //   workgroup or none (3600 x 384 x 1536 BF16 19.0 -> 10.1, FP8 12.6 -> 7.5;
   //   576 x 384 x 1536 18.0 -> 8.4; 3600 x 1152 x 384, 1026 tiles, 9.0 against 8.4
@@ -1205,7 +1205,7 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   } else {
     if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4) {
       // Five tile forms, by how many tiles they give the 256 CUs (us on one
-      // box for M x N x K, with the FP32-MFMA kernel these replace first):
+      // card for M x N x K, with the FP32-MFMA kernel these replace first):
       //  32 x 32, 4 waves in 4 k groups, while its tiles are at most one per CU
       //   (latency: a workgroup reads a third less than a 64 x 32 one, and two
       //   networks' workgroups fit one CU: 576 x 384 x 1536 54.0 -> 14.8, 64 x 32
