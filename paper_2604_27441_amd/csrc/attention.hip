@@ -417,9 +417,12 @@ __global__ __launch_bounds__(NT, 3) void attn_kernel(const AttnArgs a) {
 // two waves on every SIMD), small ones 1 wave x 6 groups (32 queries), whose
 // waves share nothing until the merge and so need no barriers.
 //
-// The scores come out times 2^48 and the probabilities times 2^24, both undone
-// for free (the shift by the max is a multiply-add; the output divides by a
-// row sum with the same factor).  A row whose result is not finite (an
+// The scores come out times 2^48, undone for free (the shift by the max is a
+// multiply-add).  The probabilities are taken at their own size and then times
+// 2^24, undone by the row sum, which has the same factor: 24 added to the
+// exponent instead would save that product, but an exponent near 24 has only 19
+// bits behind its point (a probability near 1 is then off by up to 6.6e-7; two
+// keys 6e-8 -> 3e-7 against 64 bits, 576 with small scores 4.4e-7 -> 5.6e-7).  A row whose result is not finite (an
 // infinity or NaN among its operands, or scores past 2^80) is computed again
 // by FP32 MFMAs (attn_f32_row_tile).
 
@@ -622,7 +625,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem&
       asm volatile("" : "+v"(oacc[0]), "+v"(oacc[1]));
     }
     // probabilities times 2^24, row sum, O^T += V^T P^T
-    const float sh = 24.0f - m_run;
+    const float sh = -m_run;
     float l0 = 0.0f, l1 = 0.0f;
 #pragma unroll
     for (int st = 0; st < NST; ++st)
@@ -631,8 +634,8 @@ __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem&
         uint32_t pw[3][4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(s[st][8 * g + 2 * e], 0x1p-48f, sh));
-          const float p1 = __builtin_amdgcn_exp2f(fmaf(s[st][8 * g + 2 * e + 1], 0x1p-48f, sh));
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(s[st][8 * g + 2 * e], 0x1p-48f, sh)) * 0x1p24f;
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(s[st][8 * g + 2 * e + 1], 0x1p-48f, sh)) * 0x1p24f;
           l0 += p0;
           l1 += p1;
           split3(p0, p1, pw[0][e], pw[1][e], pw[2][e]);

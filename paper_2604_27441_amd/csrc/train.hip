@@ -873,7 +873,7 @@ __global__ __launch_bounds__(TB, 2) void attn_bwd_dkdv_kernel(const AttnBwdArgs 
     bw_land(qp, pq);
     bw_land(dp_, pd);
     if (tid < 64) {
-      lse_s[tid] = 24.0f - pl;
+      lse_s[tid] = -pl;
       dv_s[tid] = pv;
     }
     __syncthreads();
@@ -904,7 +904,7 @@ __global__ __launch_bounds__(TB, 2) void attn_bwd_dkdv_kernel(const AttnBwdArgs 
         for (int k = 0; k < 2; ++k) {
           const int i = 8 * g + 2 * e + k, ql = 32 * qh + acc_row(i, lane);
           chk = fmaf(sc[i], 0.0f, chk);
-          p[k] = __builtin_amdgcn_exp2f(fmaf(sc[i], 0x1p-48f, lse_s[ql]));
+          p[k] = __builtin_amdgcn_exp2f(fmaf(sc[i], 0x1p-48f, lse_s[ql])) * 0x1p24f;
           ds[k] = p[k] * fmaf(dp[i], 0x1p-48f, -dv_s[ql]);
         }
         split3(p[0], p[1], pw[0][e], pw[1][e], pw[2][e]);
@@ -1013,8 +1013,9 @@ __global__ __launch_bounds__(TB, 2) void attn_bwd_dq_kernel(const AttnBwdArgs a)
   bf16x8 qf[4][3], df[4][3];
   bw_row_frags(qf, qrs, (base + q0 + ql) * 64, half);
   bw_row_frags(df, drs, (base + q0 + ql) * dpitch, half);
-  const float lse = 24.0f - (ql < nq ? a.lse[(size_t)h * a.ld + base + q0 + ql] : 0.0f);
-  const float dvq = ql < nq ? a.dv[(size_t)h * a.ld + base + q0 + ql] : 0.0f;
+  const float lse = ql < nq ? -a.lse[(size_t)h * a.ld + base + q0 + ql] : 0.0f;
+  // times 2^24, so that dS comes out scaled
+  const float dvq = ql < nq ? a.dv[(size_t)h * a.ld + base + q0 + ql] * 0x1p24f : 0.0f;
   f32x16 gq[2] = {};
   float chk = 0.0f;
   for (int k0 = 0; k0 < N; k0 += 64) {
@@ -1041,7 +1042,7 @@ __global__ __launch_bounds__(TB, 2) void attn_bwd_dq_kernel(const AttnBwdArgs a)
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       chk = fmaf(sc[i], 0.0f, chk);
-      ds[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], 0x1p-48f, lse)) * fmaf(dp[i], 0x1p-48f, -dvq);
+      ds[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], 0x1p-48f, lse)) * fmaf(dp[i], 0x1p-24f, -dvq);
     }
     if (k0 + 64 > N)
 #pragma unroll

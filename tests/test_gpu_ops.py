@@ -249,6 +249,23 @@ def test_attention_fp32_tiles(heads, ntok):
         assert np.abs(got[:ntok, h * 64:(h + 1) * 64] - ref).max() < 2e-5 * np.abs(v64[h]).max()
 
 
+# both FP32 tile forms (32 and 128 queries)
+@pytest.mark.parametrize("heads,ntok", [(6, 2), (6, 8), (6, 64), (129, 64), (2, 300), (33, 300)])
+def test_attention_fp32_small_scores(heads, ntok):
+    """Probabilities near each other are as exact as FP32 holds them.  Per
+    output, as independent errors uniform over +-2^-24 of their value: the exp2
+    (1 ulp, twice that range), the partial products that are left out, one
+    rounding for each of the six products of every 16 keys, and the row sum,
+    its reciprocal, the product with it and the score."""
+    qd, kd, vt, q64, k64, v64, ld = _attn_inputs(heads, ntok, FP32, scale=0.1)
+    o = torch.zeros((ntok, heads * 64), dtype=torch.float32).cuda()
+    assert _lib().revo_op_attention(FP32, qd.data_ptr(), kd.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok, ld, None) == 0
+    got = o.double().cpu().numpy()
+    ref = np.concatenate([oracle.attention_head(q64[h], k64[h], v64[h]) for h in range(heads)], axis=1)
+    rms = np.sqrt(np.mean((got - ref) ** 2) / np.mean(ref ** 2))
+    assert rms <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(4 + 1 + 6 * ((ntok + 15) // 16) + 4), rms
+
+
 @pytest.mark.parametrize("heads,ntok", [(1, 300), (33, 300)])   # 32- and 128-query tiles
 def test_attention_fp32_range(heads, ntok):
     """FP32 operands over the whole range: a key whose scores are -inf counts
