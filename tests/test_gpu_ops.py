@@ -167,6 +167,25 @@ def test_linear_tile_forms_agree(prec, epi, M, N, K):
     assert torch.equal(out.view(torch.uint8), parts.view(torch.uint8))
 
 
+# the residual forms: 64 x 64, 128 x 128 on 8 and on 4 waves, 256 x 64 tiles
+@pytest.mark.parametrize("M,N,K", [(300, 384, 1536), (8005, 384, 1536), (22021, 384, 384), (20007, 192, 768)])
+def test_linear_bf16_residual_of_a_large_bias(M, N, K):
+    """A bias of 1000 times the products: the sum of the products keeps its own
+    precision (a rounding of 2^-24 of itself every 16 of K), then two roundings
+    at the size of the result."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    w = (torch.randn((N, K), generator=g, device="cuda") * math.sqrt(1.0 / K)).bfloat16()
+    b = 1000.0 * torch.randn((N,), generator=g, device="cuda")
+    out = torch.zeros((M, N), device="cuda")
+    assert _lib().revo_op_linear(BF16, 1, x.data_ptr(), w.data_ptr(), b.data_ptr(), out.data_ptr(), M, N, K, None) == 0
+    torch.cuda.synchronize()
+    sums = x.double() @ w.double().T.contiguous()
+    ref = sums + b.double()
+    tol = 2.0 ** -24 * (2 * ref.abs() + K / 16 * float(sums.abs().max()))
+    assert bool(((out.double() - ref).abs() <= tol).all()), float(((out.double() - ref).abs() / tol).max())
+
+
 @pytest.mark.parametrize("prec", [FP32, BF16])
 @pytest.mark.parametrize("rows,D", [(1, 384), (1000, 384), (333, 192), (5, 24)])
 def test_layernorm(prec, rows, D):
