@@ -1169,20 +1169,24 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   if ((long long)gm * BM * a.K * esz >= (1LL << 31) || (long long)a.N * a.K * esz >= (1LL << 31)) return -22;
   // Dense BF16 products (all but the head) and FP8 products whose K is a
   // multiple of 128 take the LDS-ring kernel, two stages.  Its tile forms give
-  // the same results bit for bit; which is chosen (us on one card, M x N x K):
-  //  64 x 64 on 4 waves while 128-wide tiles would leave most CUs with one
-  //   workgroup or none (3600 x 384 x 1536 BF16 19.0 -> 10.1, FP8 12.6 -> 7.5;
-  //   576 x 384 x 1536 18.0 -> 8.4; 3600 x 1152 x 384, 1026 tiles, 9.0 against 8.4
-  //   with the next form);
-  //  BF16: 128 x 128 on 8 waves of 64 x 32, four waves per SIMD (43200 x 1536 x
-  //   384 GELU 84 -> 82, now 75, 3600 x 1152 x 384 8.8 -> 8.4, 10800 x 384 x 1536 25.2 ->
-  //   23.2), but 4 waves of 64 x 64 for the residual epilogue beyond two
-  //   workgroups per CU (43200 x 384 x 384 34.5, 40 on 8 waves);
-  //  FP8, whose stages hold twice the K: 128 x 64 on 4 waves, three workgroups
-  //   per CU (10800 x 384 x 1536 17.2 -> 15.0, 43200 x 1536 x 384 69 -> 65), but
-  //   128 x 128 for large plain stores (86400 x 1152 x 384 62 - 66, 71 at 128 x
-  //   64);
-  //  N not a multiple of 128: 256 x 64 on 8 waves (BF16) or 128 x 64 (FP8)
+  // the same results bit for bit.  Which is taken, each with a shape's us in it
+  // and in the next best one (M x N x K; captured launches on one card, buffers
+  // out of cache):
+  //  64 x 64 on 4 waves up to 700 tiles of it, where larger ones leave CUs idle
+  //   (3600 x 384 x 1536, 342 tiles: BF16 21.2 and 27.0, FP8 9.8 and 13.0; 2304 x
+  //   1152 x 384, 648: BF16 6.0 and 7.0, FP8 5.0 and 5.5).  They stop winning
+  //   between there and 1350 tiles (14400 x 384 x 384: BF16 23.6 and 18.6);
+  //  BF16 beyond: 128 x 128 on 8 waves of 64 x 32, four waves per SIMD (10800 x
+  //   1536 x 384 GELU 21.9, on 4 waves 22.5; 43200 x 384 x 384 residual 43.8 and
+  //   45.2; 43200 x 1152 x 384 50.5 and 49.8), or 256 x 64 on 8 waves where N is
+  //   not a multiple of 128 (43200 x 576 x 192 18.6, 128 x 64 19.7);
+  //  FP8 beyond, whose stages hold twice the K: 128 x 64 on 4 waves, three
+  //   workgroups per CU (14400 x 1536 x 384 GELU 23.3, 128 x 128 24.0; 7400 x 1152
+  //   x 384 9.0 and 10.6; 43200 x 192 x 384 10.3, 256 x 64 11.7), but 128 x 128 on
+  //   4 waves for plain stores past 700 of its tiles (43200 x 1152 x 384 35.3,
+  //   128 x 64 37.1) and for residuals past 384, where 128 x 64 would be more than
+  //   one round of three per CU (16384 x 384 x 1536 26.8, 26.2; 16500 26.4, 31.5;
+  //   21600 29.1, 37.2; 43200 58.0, 66.0)
   constexpr bool RING = XM == X_DENSE && EPI != EPI_HEAD && sizeof(typename Op::T) <= 2;
   if constexpr (RING) {
     constexpr bool B16 = sizeof(typename Op::T) == 2;
@@ -1195,12 +1199,10 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
         gemm_dma_kernel<Op, 64, 64, 2, 2, 2, 4, EPI, OutT><<<dim3((unsigned)t64), 256, 0, s>>>(a);
       else if (a.N % 128 && B16)
         gemm_dma_kernel<Op, 256, 64, 4, 2, 2, 1, EPI, OutT><<<dim3(gm2 * (a.N / 64)), 512, 0, s>>>(a);
-      else if (a.N % 128 || (!B16 && (RES || GEL || t128 < 700)))
+      else if (a.N % 128 || (!B16 && (GEL || t128 <= (RES ? 384 : 700))))
         gemm_dma_kernel<Op, 128, 64, 2, 2, 2, 3, EPI, OutT><<<dim3(gm * (a.N / 64)), 256, 0, s>>>(a);
-      else if (B16 && (!RES || t128 <= 512))
-        gemm_dma_kernel<Op, 128, 128, 2, 4, 2, 4, EPI, OutT><<<dim3((unsigned)t128), 512, 0, s>>>(a);
       else
-        gemm_dma_kernel<Op, 128, 128, 2, 2, 2, 2, EPI, OutT><<<dim3((unsigned)t128), 256, 0, s>>>(a);
+        gemm_dma_kernel<Op, 128, 128, 2, B16 ? 4 : 2, 2, B16 ? 4 : 2, EPI, OutT><<<dim3((unsigned)t128), B16 ? 512 : 256, 0, s>>>(a);
       return hipGetLastError() == hipSuccess ? 0 : -5;
     }
   }
@@ -1208,24 +1210,24 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
     return -22;  // not reached: every BF16 dense product takes the ring
   } else {
     if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4) {
-      // Five tile forms, by how many tiles they give the 256 CUs (us on one
-      // card for M x N x K, with the FP32-MFMA kernel these replace first):
-      //  32 x 32, 4 waves in 4 k groups, while its tiles are at most one per CU
-      //   (latency: a workgroup reads a third less than a 64 x 32 one, and two
-      //   networks' workgroups fit one CU: 576 x 384 x 1536 54.0 -> 14.8, 64 x 32
-      //   17.8; 576 x 384 x 384 5.8, 6.7; the 256 x 192 recovery of two networks
-      //   1388 -> 1328; 800 x 384 x 1536, 300 tiles, 20.0 against 18.3 with the
-      //   next form; 8 waves in 8 k groups with 96 KB of LDS 12.6 alone, but the
-      //   recovery 1296 where this one takes 1277);
-      //  64 x 32, 8 waves in 4 k groups, while its tiles are at most one per
-      //   CU (latency: 576 x 384 x 1536 54.0 -> 18.6; 64 x 64 26.3);
-      //  128 x 64, 8 waves in 2 k groups, from 160 to 256 tiles, about one per
-      //   CU (4608 x 384 x 1536 56.6 -> 43.1; 64 x 64 45.2, 128 x 128 81.8);
-      //  64 x 64, 8 waves in 2 k groups, up to 700 tiles (2304 x 1152 x 384
-      //   31.2 -> 18.9; 128 x 64 21.2, 128 x 128 25.4);
-      //  128 x 128, 4 waves, from 384 tiles (43200 x 1536 x 384 445 -> 298;
-      //   128 x 64 339), and 128 x 64 in between (10800 x 384 x 1536 109 -> 80;
-      //   128 x 128 87)
+      // Five tile forms, by how many tiles they give the 256 CUs, each with a
+      // shape's us in it and in its neighbour (M x N x K; captured launches on
+      // one card):
+      //  32 x 32, 4 waves in 4 k groups, while its tiles are at most one per CU:
+      //   latency counts, and a workgroup reads a third less than a 64 x 32 one
+      //   (576 x 384 x 1536, 216 tiles, 15.5 and 18.6; on FP32 MFMAs 55.7; 800 x
+      //   384 x 1536, 300 tiles, 20.5 and 18.8);
+      //  64 x 32, 8 waves in 4 k groups, while its tiles are at most one per CU
+      //   (448 x 1152 x 384, 252 tiles, 7.8, 64 x 64 9.5; 576 x 1152 x 384, 324
+      //   tiles, 10.5 and 9.7);
+      //  128 x 64, 8 waves in 2 k groups, from 160 to 256 tiles, about one per CU
+      //   (1152 x 1152 x 384 13.5, 64 x 64 13.9; 10800 x 192 x 192 12.6 and 15.5;
+      //   not at 4608 x 384 x 384, 17.2 and 15.6);
+      //  64 x 64, 8 waves in 2 k groups, up to 700 tiles (2304 x 1152 x 384, 648,
+      //   20.1, 128 x 64 23.1; 2900 x 1152 x 384, 828, 25.9 and 24.4);
+      //  128 x 128, 4 waves, from 384 tiles (5000 x 1536 x 384, 480, 43.8, 128 x 64
+      //   47.5; 43200 x 1536 x 384 320 and 350, on FP32 MFMAs 462), and 128 x 64 in
+      //   between (3600 x 1536 x 384, 348 tiles of 128 x 128, 37.3 and 41.5)
       const long long gm64 = cdiv(a.M, 64);
       const long long t6432 = gm64 * (a.N / 32), t6464 = gm64 * (a.N / 64), t12864 = (long long)gm * (a.N / 64);
       const long long t128 = a.N % 128 == 0 ? (long long)gm * (a.N / 128) : 0;

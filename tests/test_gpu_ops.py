@@ -167,7 +167,14 @@ def test_linear_tile_forms_agree(prec, epi, M, N, K):
     assert torch.equal(out.view(torch.uint8), parts.view(torch.uint8))
 
 
-# the residual forms: 64 x 64, 128 x 128 on 8 and on 4 waves, 256 x 64 tiles
+# both sides of the line at which FP8 residual products go from 128 x 64 to 128 x
+# 128 tiles (384 of the larger), and BF16 ones of more than two 128 x 128 tiles per CU
+@pytest.mark.parametrize("prec,M,N,K", [(2, 16384, 384, 384), (2, 16385, 384, 128), (BF16, 21900, 384, 128)])
+def test_residual_tile_forms_agree(prec, M, N, K):
+    test_linear_tile_forms_agree(prec, 1, M, N, K)
+
+
+# the residual forms: 64 x 64, 128 x 128 and 256 x 64 tiles
 @pytest.mark.parametrize("M,N,K", [(300, 384, 1536), (8005, 384, 1536), (22021, 384, 384), (20007, 192, 768)])
 def test_linear_bf16_residual_of_a_large_bias(M, N, K):
     """A bias of 1000 times the products: the sum of the products keeps its own
