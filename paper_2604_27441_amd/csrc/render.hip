@@ -61,25 +61,42 @@ __device__ __forceinline__ bool project_point(const float4& p, unsigned n, const
   return true;
 }
 
-// Splat of one tile of SW x SH source points, grid (tiles across, tiles down,
-// frames).  What bounds it is the rate of atomics on the z-buffer's lines: 64
-// neighbouring points land on pieces of some 30 lines, and one atomic per
-// point took 60 us for four 1280x720 frames (61 G atomics/s; this form 31).  The
-// tile's target pixels mostly fill a small box, so its points first meet in a
-// z-buffer of that box in LDS, and the box's winners then go to the z-buffer row
-// by row, whole lines per wave.  A box that does not fit (a depth edge, noise in
-// the depth, a strong rotation) is cut to the columns around its points' mean,
-// and the other points, or all of a box too tall for that, go to the z-buffer
-// themselves.  The minimum is the same either way.  16 KB of LDS, so that
-// occupancy is 8 workgroups: unprojection and view of four smooth frames 91 us
-// with an atomic per point, 66 with 32 KB and no cut, 62 as it is (buffers in
-// cache; 98.8, 73.4 and 69.9 out of it), a fifth of the depth noise 94, 70.5, 68;
-// frames with much of the depth missing, whose atomics are few, 59, 64.5, 61.
-constexpr int SW = 64, SH = 16, SPT = SW * SH / RT, SBOX = 2048;
+// Splat of one tile of 64 x 4 SPT source points, grid (tiles across, tiles down,
+// frames), wave w taking rows w, w + 4, ...  What bounds a large launch is the
+// rate of atomics on the z-buffer's lines: in a turned view 64 neighbouring
+// points land on pieces of some 30 lines, and one atomic per point takes 79 us
+// with four 1280x720 frames (clear, splat and resolve).  The tile's target
+// pixels mostly fill a small box, so its points first meet in a z-buffer of that
+// box in LDS, and the box's winners then go to the z-buffer row by row, whole
+// lines per wave: 50 us.  A box that does not fit (a depth edge, noise in the
+// depth, a strong rotation) is cut to the columns around its points' mean, and
+// the other points, or all of a box too tall for that, go to the z-buffer
+// themselves.
+// The box costs a wave two more barriers and a pass over its pixels, so a wave
+// whose atomics are cheap already sends its points itself: those whose points,
+// per lane, continue on their left neighbour's line and rarely on its very
+// pixel (atomics on one pixel take turns).  Frames of 400 000 points or fewer
+// never fill the chip, so they take one row per wave, count no lines and box
+// only points that collide.  us with an atomic per point, with a box for every
+// tile of 64 x 16, and as it is (captured launches; the view is 100 mm aside and 5
+// degrees off unless said): four 1280x720 frames 79, 51, 50,
+// unmoved 44, 48, 43, at half size 83, 28, 29, a tenth of the points valid 34.6,
+// 39.5, 33.8, depth all noise 91, 80, 75; one 640x480 frame 11.7, 12.0, 11.6,
+// unmoved 8.9, 10.9, 9.0, 6 m back 21.6, 11.8, 15.4; one 256x192 frame 6.1, 8.7,
+// 6.2.  Behind the atomic per point by 5 to 8 %: one unmoved 1280x720 frame 14.0,
+// 16.3, 14.7, two 640x480 frames of patches of a fifth of the points 11.3, 13.5,
+// 12.1, four frames of much missing depth 400 mm nearer 40.6, 46.2, 42.6.
+// The minimum is the same by every way.  16 KB of LDS leave 8 workgroups per CU.
+constexpr int SW = 64, SBOX = 2048;
+constexpr long long SMALL_SPLAT = 400000;  // points
+template <int SPT>
 __global__ __launch_bounds__(RT) void splat_kernel(const float4* __restrict__ pts, int H, int W, Pose P, Intr k,
                                                    int Ho, int Wo, unsigned long long* __restrict__ zbuf) {
+  constexpr int SH = 4 * SPT;
+  // most new lines and repeated pixels of a wave's points that still go themselves
+  constexpr int MAX_LINES = SPT == 1 ? 64 : 28, MAX_SAME = SPT == 1 ? 24 : 8;
   __shared__ unsigned long long box[SBOX];
-  __shared__ int ext[4][RT / 64];
+  __shared__ int ext[4][RT / 64], boxed[RT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int u = blockIdx.x * SW + lane;
   const float4* src = pts + (long long)blockIdx.z * H * W;
@@ -105,12 +122,37 @@ __global__ __launch_bounds__(RT) void splat_kernel(const float4* __restrict__ pt
       v1 = max(v1, iv[i]);
     }
   }
+  int lines = 0, same = 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    u0 = min(u0, __shfl_xor(u0, o));
-    u1 = max(u1, __shfl_xor(u1, o));
-    v0 = min(v0, __shfl_xor(v0, o));
-    v1 = max(v1, __shfl_xor(v1, o));
+  for (int i = 0; i < SPT; ++i) {
+    // (in a wave of 64 the lanes without a neighbour in their row of 16 count as
+    // a new line; a line is 8 pixels, rows need not start on one)
+    const unsigned px = ok[i] ? (unsigned)iv[i] * Wo + iu[i] : ~0u;
+    const unsigned left = (unsigned)__builtin_amdgcn_update_dpp(-1, (int)px, 0x111, 0xF, 0xF, false);
+    lines += __popcll(__ballot(ok[i] && (px ^ left) >= 8u));
+    same += __popcll(__ballot(ok[i] && px == left));
+  }
+  const bool direct = lines <= MAX_LINES && same <= MAX_SAME;
+  if (direct) {
+#pragma unroll
+    for (int i = 0; i < SPT; ++i) {
+      if (ok[i]) atomicMin(dst + (long long)iv[i] * Wo + iu[i], key[i]);
+      ok[i] = false;
+    }
+  }
+  if (lane == 0) boxed[wave] = !direct;
+  __syncthreads();
+  if (!(boxed[0] | boxed[1] | boxed[2] | boxed[3])) return;
+  if (direct) {
+    u0 = Wo; u1 = -1; v0 = Ho; v1 = -1;
+  } else {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      u0 = min(u0, __shfl_xor(u0, o));
+      u1 = max(u1, __shfl_xor(u1, o));
+      v0 = min(v0, __shfl_xor(v0, o));
+      v1 = max(v1, __shfl_xor(v1, o));
+    }
   }
   if (lane == 0) {
     ext[0][wave] = u0;
@@ -233,8 +275,11 @@ int launch_render_view(const float* pts, const uint8_t* rgb, int B, int H, int W
   const long long nz = (long long)B * Ho * Wo;
   if (cdivll(nz, RT) > 0x7fffffffLL) return -22;
   zbuf_clear_kernel<<<(unsigned)cdivll(nz, RT), RT, 0, s>>>(zbuf, nz);
-  splat_kernel<<<dim3(cdiv(W, SW), cdiv(H, SH), B), RT, 0, s>>>(reinterpret_cast<const float4*>(pts), H, W, P, k, Ho, Wo,
-                                                               zbuf);
+  const float4* p4 = reinterpret_cast<const float4*>(pts);
+  if ((long long)B * H * W <= SMALL_SPLAT)
+    splat_kernel<1><<<dim3(cdiv(W, SW), cdiv(H, 4), B), RT, 0, s>>>(p4, H, W, P, k, Ho, Wo, zbuf);
+  else
+    splat_kernel<2><<<dim3(cdiv(W, SW), cdiv(H, 8), B), RT, 0, s>>>(p4, H, W, P, k, Ho, Wo, zbuf);
   resolve_kernel<<<dim3(cdiv(Wo, RT), Ho, B), RT, 0, s>>>(zbuf, rgb, H, W, Ho, Wo, rgb_out, depth_out);
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }

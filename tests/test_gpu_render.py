@@ -160,6 +160,27 @@ def test_zoomed_view(zoom, H, W):
         assert np.array_equal(w[b], rw) and np.array_equal(c[b], rc) and np.array_equal(d[b], rd)
 
 
+# frames of at most 400 000 points (one row per wave) and of more (two)
+@pytest.mark.parametrize("B,H,W", [(2, 35, 130), (2, 330, 611)])
+@pytest.mark.parametrize("zoom", [8.0, 2.0, 1.0, 0.5, 0.25])
+def test_zoomed_view_of_mixed_rows(B, H, W, zoom):
+    """As test_zoomed_view, with every other row thinned to one pixel in eight:
+    waves of one workgroup whose points go to the z-buffer themselves beside
+    waves whose points meet in LDS (at 0.25 four of a row on every pixel)."""
+    depth = RNG.integers(500, 3000, (B, H, W)).astype(np.uint16)
+    depth[:, ::2, np.arange(W) % 8 != 3] = 0
+    rgb = RNG.integers(0, 256, (B, H, W, 3)).astype(np.uint8)
+    intr = (float(W), float(W), 0.0, 0.0)
+    Ho, Wo = int(H * zoom) + 3, int(W * zoom) - 2
+    c0 = {0.5: -0.25, 0.25: -0.375}.get(zoom, 0.25)
+    view = (W * zoom, W * zoom, c0, c0)
+    pose = np.hstack([np.eye(3), np.zeros((3, 1))])
+    c, d, w = _render(_unproject(depth, intr), rgb, pose, view, Ho, Wo)
+    for b in range(B):
+        rc, rd, rw = oracle.render_view(oracle.unproject(depth[b], intr), rgb[b], pose, view, Ho, Wo)
+        assert np.array_equal(w[b], rw) and np.array_equal(c[b], rc) and np.array_equal(d[b], rd)
+
+
 def test_moved_view_720p():
     rgb, depth = synth.scene_frames(1003, 720, 1280, [4, 5])
     intr = (1280.0, 1280.0, 639.5, 359.5)
