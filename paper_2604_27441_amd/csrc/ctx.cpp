@@ -26,6 +26,7 @@
 #include "../../include/revo.h"
 #include "model.h"
 #include "sched.h"
+#include "side_thread.h"
 
 using namespace revo;
 
@@ -160,12 +161,7 @@ struct revo_ctx {
   // worker enqueues the RGB one (two streams, no graphs): a network is about
   // 115 launches, and one thread issuing both left the depth stream idle until
   // the RGB network was enqueued (a 256x192 pair: 1639 -> 1340 us FP32).
-  std::thread enqueuer;
-  std::mutex enq_mu;
-  std::condition_variable enq_cv;
-  InFlightPtr enq_batch = nullptr;  // posted by the worker, cleared by the enqueuer (guarded by enq_mu)
-  int enq_rc = 0;
-  bool enq_stop = false;
+  SideThread enqueuer;
   std::deque<InFlightPtr> inflight;          // batches on the GPU, oldest first
   std::vector<int> free_slots;               // host descriptor slots not in flight
   std::condition_variable cv_inflight;
@@ -371,39 +367,13 @@ int launch_mod(revo_ctx* c, InFlight* f, int q) {
   return rc;
 }
 
-void enqueuer_main(revo_ctx* c) {
-  (void)hipSetDevice(c->cfg.device);
-  std::unique_lock<std::mutex> lk(c->enq_mu);
-  for (;;) {
-    c->enq_cv.wait(lk, [&] { return c->enq_batch || c->enq_stop; });
-    if (!c->enq_batch) return;
-    InFlight* f = c->enq_batch;
-    lk.unlock();
-    const int rc = launch_mod(c, f, 1);
-    lk.lock();
-    c->enq_rc = rc;
-    c->enq_batch = nullptr;
-    c->enq_cv.notify_all();
-  }
-}
-
 // Enqueue one batch on the modality streams.
 int launch_batch(revo_ctx* c, InFlight* f) {
-  const bool both = c->enqueuer.joinable() && has_mod(f, 0) && has_mod(f, 1);
-  if (both) {
-    std::lock_guard<std::mutex> lk(c->enq_mu);
-    c->enq_batch = f;
-    c->enq_cv.notify_all();
-  }
-  int rc = launch_mod(c, f, 0);
-  if (both) {
-    std::unique_lock<std::mutex> lk(c->enq_mu);
-    c->enq_cv.wait(lk, [&] { return c->enq_batch == nullptr; });
-    if (c->enq_rc) rc = c->enq_rc;
-  } else if (int e = launch_mod(c, f, 1)) {
-    rc = e;
-  }
-  return rc;
+  auto rgb = [&] { return launch_mod(c, f, 0); };
+  auto depth = [&] { return launch_mod(c, f, 1); };
+  if (has_mod(f, 0) && has_mod(f, 1)) return c->enqueuer.run(rgb, depth);
+  const int a = rgb(), b = depth();
+  return b ? b : a;
 }
 
 // Wait for a batch, copy host outputs, post its completions.
@@ -772,9 +742,15 @@ int revo_recover_create(const revo_config* cfg_in, revo_ctx** out) {
   c->inflight_max = (cfg.flags & (REVO_CFG_PROFILE | REVO_CFG_PROFILE_ATTN)) ? 1 : WS_SLOTS;
   c->use_graphs = (cfg.flags & REVO_CFG_GRAPHS) != 0;
   for (int sl = 0; sl < c->inflight_max; ++sl) c->free_slots.push_back(sl);
-  if (nstreams == 2 && !c->use_graphs) c->enqueuer = std::thread(enqueuer_main, c);
-  c->worker = std::thread(worker_main, c);
-  c->completer = std::thread(completer_main, c);
+  // (without the enqueuer the worker enqueues both networks itself)
+  if (nstreams == 2 && !c->use_graphs) (void)c->enqueuer.start([c] { (void)hipSetDevice(c->cfg.device); });
+  try {
+    c->worker = std::thread(worker_main, c);
+    c->completer = std::thread(completer_main, c);
+  } catch (const std::system_error&) {
+    revo_recover_destroy(c);
+    return REVO_ENOMEM;
+  }
   *out = c;
   return REVO_OK;
 }
@@ -917,14 +893,7 @@ void revo_recover_destroy(revo_ctx* c) {
   }
   c->cv_work.notify_all();
   if (c->worker.joinable()) c->worker.join();
-  if (c->enqueuer.joinable()) {
-    {
-      std::lock_guard<std::mutex> lk(c->enq_mu);
-      c->enq_stop = true;
-    }
-    c->enq_cv.notify_all();
-    c->enqueuer.join();
-  }
+  c->enqueuer.stop();
   {
     std::lock_guard<std::mutex> lk(c->mu);
     c->completer_stop = true;
