@@ -131,6 +131,29 @@ def test_linear_fp32_range(M, N, K):
     assert np.all(err <= 2e-6 * math.sqrt(K) * rowmax + 2.0 ** -148)
 
 
+def _fp32_form(M, N, K):
+    """The tile form that gemm.hip's rule takes for an FP32 product."""
+    def tiles(bm, bn):
+        return -(-M // bm) * (N // bn)
+    if tiles(32, 32) <= 256 and K % 64 == 0:
+        return "32x32"
+    if tiles(64, 32) <= 256 and K % 64 == 0:
+        return "64x32"
+    if tiles(64, 64) <= 700 and not 160 <= tiles(128, 64) <= 256:
+        return "64x64"
+    return "128x128" if N % 128 == 0 and tiles(128, 128) >= 384 else "128x64"
+
+
+FP32_FORMS = [("32x32", 100, 64, 128), ("64x32", 1000, 384, 128), ("64x64", 2300, 384, 64), ("128x64", 3000, 512, 64),
+              ("128x128", 6200, 1024, 64)]
+
+
+@pytest.mark.parametrize("form,M,N,K", FP32_FORMS)
+def test_linear_fp32_range_of_every_form(form, M, N, K):
+    assert _fp32_form(M, N, K) == form
+    test_linear_fp32_range(M, N, K)
+
+
 # shapes beyond the 64 x 64 tiles: BF16 on 128 x 128 (8 waves; 4 waves for the
 # large residual one) and 256 x 64, FP8 on 128 x 64 and 128 x 128
 @pytest.mark.parametrize("prec,epi,M,N,K", [

@@ -127,6 +127,60 @@ def test_batch_invariance_and_host_pointers():
             assert np.array_equal(host[key], alone[2][key]), key
 
 
+@pytest.mark.parametrize("prec,n", [(BF16, 5), (BF16, 20), (2, 5), (2, 20), (FP32, 2), (FP32, 4), (FP32, 8)])
+def test_batches_that_take_other_tile_forms(prec, n):
+    """A 256 x 192 request (576 tokens) alone and beside n - 1 others, whose
+    rows together take other tile forms of the products, the Q / K / V split
+    and transposed V with them: BF16 64 x 64 alone, 128 x 128 at 5 and 256 x 64
+    (decoder) at 20, FP8 64 x 64, 128 x 64 and 128 x 128.  Those give the same
+    bits.  The FP32 forms sum K in four groups, two or one, by the rows of the
+    whole batch, so a request's FP32 result depends on its batch, by rounding
+    alone: no further apart than twice what either may be from the oracle."""
+    import torch
+    from tests.gpu_util import dev
+    blobs = synth.make_weights(3, perturb_seed=4, enc_depth=1, dec_depth=1)
+    req = synth.make_request(121, 122, 192, 256, loss=("stripes", 0.4))
+    other = synth.make_request(123, 124, 192, 256, loss=("stripes", 0.4))
+    cap = 20 * 576
+    big = synth.make_request(125, 126, 768, 1280, loss=("stripes", 0.4))   # 11520 tokens, a whole batch
+
+    def buffers(r):
+        h, w = r["height"], r["width"]
+        return ([dev(r["rgb"]), dev(r["mask_rgb"]), dev(r["depth"]), dev(r["mask_depth"])],
+                dict(rgb=torch.zeros((h, w, 3), dtype=torch.uint8, device="cuda"),
+                     depth=torch.zeros((h, w), dtype=torch.int16, device="cuda"),
+                     rgb_f=torch.zeros((h, w, 3), device="cuda"), depth_f=torch.zeros((h, w), device="cuda")))
+
+    with _rec(blobs, prec, enc_depth=1, dec_depth=1, max_batch=24, max_batch_tokens=cap) as rec:
+        if prec == 2:
+            push_refs(rec, 30, req)
+            rec.calibrate(1)
+            recover(rec, [(30, req)])
+            rec.calibrate(0)
+        push_refs(rec, 40, big)
+        # the small requests queue behind whole batches and then go together
+        items = [(40, big)] * 8 + [(s, other if s else req) for s in range(n)]
+        for s in range(n):
+            push_refs(rec, s, other if s else req)
+        bufs = [buffers(r) for _, r in items]
+        torch.cuda.synchronize()
+        batches = rec.stats()["batches"]
+        tickets = [rec.submit(s, int(r["t_target"]), r["width"], r["height"], rgb=i[0], mask_rgb=i[1], depth=i[2],
+                              mask_depth=i[3], rgb_out=o["rgb"], depth_out=o["depth"], rgb_out_f32=o["rgb_f"],
+                              depth_out_f32=o["depth_f"], device_ptrs=True) for (s, r), (i, o) in zip(items, bufs)]
+        assert all(c.status == 0 for c in rec.wait(tickets).values())
+        assert rec.stats()["batches"] == batches + 9
+        mixed = {k: v.cpu().numpy() for k, v in bufs[8][1].items()}
+        mixed["depth"] = mixed["depth"].view(np.uint16)
+        alone = recover(rec, [(0, req)])[0]
+    if prec != FP32:
+        for key in ("rgb", "depth", "rgb_f", "depth_f"):
+            assert np.array_equal(mixed[key], alone[key]), key
+    else:
+        assert np.abs(mixed["rgb_f"] - alone["rgb_f"]).max() <= 2e-4
+        assert np.abs(mixed["depth_f"] - alone["depth_f"]).max() <= 1.0
+
+
 def test_references_reused_across_later_targets():
     """Two corrupted frames in a row use the same clean references; the second
     one sees a larger temporal distance (no recovered frame enters the ring)."""

@@ -245,3 +245,32 @@ def test_malformed_requests_are_refused_and_the_context_stays_usable():
         ref = oracle.recover(req, blobs, **SMALL)
         g = _np(o)
         assert np.abs(g["rgb_f"].astype(np.float64) - ref["rgb"][1]).max() <= 1e-4
+
+
+def test_graphs_are_captured_while_batches_are_waited_for():
+    """Four requests of four capacity buckets, one to a batch: while the
+    worker captures a bucket's graph the completion thread starts to wait for
+    the events of the batch before, recorded on the networks' streams.  All
+    complete, with the bytes each has alone."""
+    from paper_2604_27441_amd import Recoverer
+    blobs = synth.make_weights(0)
+    reqs = [synth.make_request(301 + i, 311 + i, h, w, loss=("stripes", 0.4))
+            for i, (h, w) in enumerate([(720, 1280), (H, W), (384, 512), (512, 704)])]   # 10800, 36, 2304, 4224 tokens
+
+    def run(together):
+        with Recoverer(blobs[0], blobs[1], precision=1, graphs=True, max_batch=1, max_batch_tokens=10880) as rec:
+            for s, r in enumerate(reqs):
+                push_refs(rec, s, r)
+            outs = [_outs(r["height"], r["width"]) for r in reqs]
+            got = {}
+            if together:
+                got = rec.wait([_submit(rec, s, r, outs[s], hold=s + 1 < len(reqs)) for s, r in enumerate(reqs)])
+            else:
+                for s, r in enumerate(reqs):
+                    got.update(rec.wait([_submit(rec, s, r, outs[s])]))
+            assert all(c.status == 0 for c in got.values()), got
+            return [_np(o) for o in outs]
+
+    for a, b in zip(run(True), run(False)):
+        for key in a:
+            assert np.array_equal(a[key], b[key]), key

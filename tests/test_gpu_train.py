@@ -197,6 +197,53 @@ def test_attention_backward_block_edges(h, w, scale):
             assert err <= 1e-4, (name, part, err)
 
 
+@pytest.mark.parametrize("scale", [106, -106])
+@pytest.mark.parametrize("h,w", [(32, 176), (48, 688)])
+def test_attention_backward_out_of_the_split_range(h, w, scale):
+    """Keys times 2^scale and queries over it leave every score alone.  At 106
+    the keys, at -106 the queries pass 2^104 in every head, beyond which the
+    split products hold no operand (a value times 2^24 is split), so both
+    kernels of the backward pass, dK and dV and dQ, do their blocks on FP32
+    MFMAs.  (test_attention_backward_block_edges at 2^100 takes dQ alone past
+    the range of the accumulators.)  Tolerances as there; the gradient of the
+    keys' bias, zero in exact arithmetic (it adds the same to all scores of a
+    query), is a sum of the rows whose products with the inputs are the weights'
+    gradient, and is held to that one's maximum."""
+    from paper_2604_27441_amd import Trainer
+    arch = oracle.Arch(channels=3, **TINY)
+    blob = synth.make_weights(5, perturb_seed=6, **TINY)[0].copy()
+    index = {k: v.astype(np.int64) for k, v in
+             oracle.unpack_weights(np.arange(blob.size, dtype=np.float64), arch).items()}
+    samples = synth.make_pretrain_batch(7, 2, h, w, 3)
+    params = oracle.unpack_weights(blob.astype(np.float64), arch)
+    for s in samples:   # the unscaled operands, as the kernels hold them
+        rec = oracle.AbsMaxRecorder()
+        oracle.forward(s["refs"], s["ref_idx"], s["target"], s["t_target"], s["mask"], params, arch, rnd=rec)
+        for head in range(6):
+            held = rec.absmax[f"enc0.attn.k{head}"] if scale > 0 else rec.absmax[f"enc0.attn.q{head}"] * oracle.QK_LOG2
+            assert held * 2.0 ** abs(scale) >= 2.0 ** 104, (head, held)
+    for name in ("enc0.qkv.w", "enc0.qkv.b"):
+        blob[index[name][:384]] *= 2.0 ** -scale
+        blob[index[name][384:768]] *= 2.0 ** scale
+    ref = ot.train_step(blob, samples, arch)
+    with Trainer(blob, 3, 2, h, w, **TINY) as tr:
+        loss = tr.step(*_dev(samples, 3))
+        grad = tr.grads()
+    assert abs(loss - ref["loss"]) <= 1e-5 * abs(ref["loss"])
+    kb = index["enc0.qkv.b"][384:768]
+    kw = index["enc0.qkv.w"][384:768].ravel()
+    assert np.abs(grad[kb]).max() <= 2e-5 * np.abs(ref["grad"][kw]).max()
+    grad[kb] = ref["grad"][kb] = 0.0
+    _check_grads(grad, ref["grad"], arch, rtol=2e-5)
+    for name in (n for n in index if n.endswith("qkv.w")):
+        rows = index[name].shape[0] // 3
+        for part in range(3):
+            i = index[name][part * rows:(part + 1) * rows].ravel()
+            want = ref["grad"][i]
+            err = np.abs(grad[i].astype(np.float64) - want).max() / np.abs(want).max()
+            assert err <= 1e-4, (name, part, err)
+
+
 def test_batch_gradient_is_the_mean_of_its_halves():
     """At batch 16 (9216 token rows, past what the oracle can check in a
     test), the loss is the batch mean, so the step's loss and gradient equal
