@@ -731,7 +731,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(const GemmArgs a) {
 
 // ---------------------------------------------------------------------------
 // Dense BF16 and FP8 form: operand stages go from HBM straight into LDS
-// (buffer loads with the LDS as destination) in a ring of NS stages, so no
+// (buffer loads with the LDS as destination) in a ring of two stages, so no
 // registers hold stages in flight and no LDS stores are issued.  A stage row
 // is 128 bytes of K (64 BF16 or 128 E4M3 values), unpadded; 16-byte chunk c
 // of row r sits at byte gswz(r, c), slot c ^ ((r >> 1) & 7), which spreads the
@@ -794,9 +794,9 @@ __device__ __forceinline__ void gemm_dma_stage(const uint8_t* __restrict__ xb, c
   }
 }
 
-// Tile BM_ tokens x BN features over WM_ x WN_ waves, NST stages of 128 bytes
-// of K, OCC waves per SIMD.
-template <class Op, int BM_, int BN, int WM_, int WN_, int NST, int OCC, int EPI, class OutT>
+// Tile BM_ tokens x BN features over WM_ x WN_ waves, two stages of 128 bytes of
+// K, OCC waves per SIMD.
+template <class Op, int BM_, int BN, int WM_, int WN_, int OCC, int EPI, class OutT>
 __global__ __launch_bounds__(64 * WM_* WN_, OCC) void gemm_dma_kernel(const GemmArgs a) {
   typedef typename Op::T T;
   constexpr int BK = 128 / (int)sizeof(T);  // K per stage
@@ -807,9 +807,9 @@ __global__ __launch_bounds__(64 * WM_* WN_, OCC) void gemm_dma_kernel(const Gemm
   constexpr int XI = XR / 8, WI = WR / 8;             // 8-row loads per wave per stage
   static_assert(XI >= 1 && WI >= 1 && MS >= 1 && NS >= 1, "tile geometry");
   constexpr int SX = BM_ * 128, SW = BN * 128;        // bytes per X / W stage
-  constexpr int OPB = NST * (SX + SW);
+  constexpr int OPB = 2 * (SX + SW);
   constexpr int EPB = epi_stage_bytes<BN, OutT, BM_>();
-  // X stages at stg + b SX, W stages at stg + NST SX + b SW; the epilogue
+  // X stages at stg + b SX, W stages at stg + 2 SX + b SW; the epilogue
   // reuses the whole array
   __shared__ __attribute__((aligned(16))) uint8_t stg[OPB > EPB ? OPB : EPB];
 
@@ -856,7 +856,7 @@ __global__ __launch_bounds__(64 * WM_* WN_, OCC) void gemm_dma_kernel(const Gemm
     _Pragma("unroll") for (int j = 0; j < XI; ++j)                                                       \
       dma16(xrs, stg + (buf_) * SX + (wave * XR + 8 * j) * 128, xo[j], (kt_) * 128);                      \
     _Pragma("unroll") for (int j = 0; j < WI; ++j)                                                       \
-      dma16(wrs, stg + NST * SX + (buf_) * SW + (wave * WR + 8 * j) * 128, wo[j], (kt_) * 128);           \
+      dma16(wrs, stg + 2 * SX + (buf_) * SW + (wave * WR + 8 * j) * 128, wo[j], (kt_) * 128);             \
   } while (0)
 
   const int wn = wave / WM_, wm = wave % WM_;
@@ -877,24 +877,20 @@ __global__ __launch_bounds__(64 * WM_* WN_, OCC) void gemm_dma_kernel(const Gemm
 #pragma unroll
       for (int k = 0; k < 16; ++k) acc[i][j][k] = BI ? cols.b[i][k >> 2][k & 3] : 0.0f;
 
-  // stage k goes to buffer k % NST, NST - 1 stages ahead
-#pragma unroll
-  for (int i = 0; i < NST - 1; ++i)
-    if (i < KT) REVO_GD_FETCH(i, i);
-  // the ring is unrolled NST times so that every buffer index is a constant
+  // stage k goes to buffer k % 2, one stage ahead (K is never 0: the branch keeps
+  // these loads in a block of their own, which the schedule of the small
+  // products wants: 576 x 192 x 384 BF16 4.74 us, 4.91 without it)
+  if (KT > 0) REVO_GD_FETCH(0, 0);
+  // unrolled twice so that every buffer index is a constant
   for (int kt = 0; kt < KT;) {
 #pragma unroll
-    for (int b = 0; b < NST; ++b) {
-      // this wave's part of stage kt is in LDS (the last stages, with fewer
-      // behind them, wait for all loads)
-      if (NST > 2 && kt + NST - 1 <= KT) wait_vm<(NST - 2) * (XI + WI)>();
-      else wait_vm<0>();
+    for (int b = 0; b < 2; ++b) {
+      wait_vm<0>();  // this wave's part of stage kt is in LDS
       // every wave's part is, and stage kt-1's buffer is free (a plain
-      // barrier: the fence of __syncthreads would also wait for the younger
-      // stage loads)
+      // barrier)
       asm volatile("s_barrier" ::: "memory");
-      if (kt + NST - 1 < KT) REVO_GD_FETCH(kt + NST - 1, (b + NST - 1) % NST);
-      gemm_dma_stage<Op, NS, MS>(stg + b * SX, stg + NST * SX + b * SW, acc, wn, wm, half, l32);
+      if (kt + 1 < KT) REVO_GD_FETCH(kt + 1, b ^ 1);
+      gemm_dma_stage<Op, NS, MS>(stg + b * SX, stg + 2 * SX + b * SW, acc, wn, wm, half, l32);
       if (++kt >= KT) break;
     }
   }
@@ -1190,60 +1186,63 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   constexpr bool RING = XM == X_DENSE && EPI != EPI_HEAD && sizeof(typename Op::T) <= 2;
   if constexpr (RING) {
     constexpr bool B16 = sizeof(typename Op::T) == 2;
-    constexpr bool RES = EPI == EPI_RESIDUAL, GEL = EPI == EPI_GELU;
     if (B16 || a.K % 128 == 0) {
       const int gm2 = cdiv(a.M, 256);
       if (a.N % 128 && (long long)gm2 * 256 * a.K * esz >= (1LL << 31)) return -22;
       const long long t64 = (long long)cdiv(a.M, 64) * (a.N / 64), t128 = (long long)gm * (a.N / 128);
-      if (t64 <= 700)
-        gemm_dma_kernel<Op, 64, 64, 2, 2, 2, 4, EPI, OutT><<<dim3((unsigned)t64), 256, 0, s>>>(a);
-      else if (a.N % 128 && B16)
-        gemm_dma_kernel<Op, 256, 64, 4, 2, 2, 1, EPI, OutT><<<dim3(gm2 * (a.N / 64)), 512, 0, s>>>(a);
-      else if (a.N % 128 || (!B16 && (GEL || t128 <= (RES ? 384 : 700))))
-        gemm_dma_kernel<Op, 128, 64, 2, 2, 2, 3, EPI, OutT><<<dim3(gm * (a.N / 64)), 256, 0, s>>>(a);
-      else
-        gemm_dma_kernel<Op, 128, 128, 2, B16 ? 4 : 2, 2, B16 ? 4 : 2, EPI, OutT><<<dim3((unsigned)t128), B16 ? 512 : 256, 0, s>>>(a);
+      if (t64 <= 700) {
+        gemm_dma_kernel<Op, 64, 64, 2, 2, 4, EPI, OutT><<<(unsigned)t64, 256, 0, s>>>(a);
+      } else if constexpr (B16) {
+        if (a.N % 128)
+          gemm_dma_kernel<Op, 256, 64, 4, 2, 1, EPI, OutT><<<gm2 * (a.N / 64), 512, 0, s>>>(a);
+        else
+          gemm_dma_kernel<Op, 128, 128, 2, 4, 4, EPI, OutT><<<(unsigned)t128, 512, 0, s>>>(a);
+      } else {
+        if (a.N % 128 || EPI == EPI_GELU || t128 <= (EPI == EPI_RESIDUAL ? 384 : 700))
+          gemm_dma_kernel<Op, 128, 64, 2, 2, 3, EPI, OutT><<<gm * (a.N / 64), 256, 0, s>>>(a);
+        else
+          gemm_dma_kernel<Op, 128, 128, 2, 2, 2, EPI, OutT><<<(unsigned)t128, 256, 0, s>>>(a);
+      }
       return hipGetLastError() == hipSuccess ? 0 : -5;
     }
   }
   if constexpr (RING && sizeof(typename Op::T) == 2) {
     return -22;  // not reached: every BF16 dense product takes the ring
+  } else if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4) {
+    // Five tile forms, by how many tiles they give the 256 CUs, each with a
+    // shape's us in it and in its neighbour (M x N x K; captured launches on
+    // one card):
+    //  32 x 32, 4 waves in 4 k groups, while its tiles are at most one per CU:
+    //   latency counts, and a workgroup reads a third less than a 64 x 32 one
+    //   (576 x 384 x 1536, 216 tiles, 15.5 and 18.6; on FP32 MFMAs 55.7; 800 x
+    //   384 x 1536, 300 tiles, 20.5 and 18.8);
+    //  64 x 32, 8 waves in 4 k groups, while its tiles are at most one per CU
+    //   (448 x 1152 x 384, 252 tiles, 7.8, 64 x 64 9.5; 576 x 1152 x 384, 324
+    //   tiles, 10.5 and 9.7);
+    //  128 x 64, 8 waves in 2 k groups, from 160 to 256 tiles, about one per CU
+    //   (1152 x 1152 x 384 13.5, 64 x 64 13.9; 10800 x 192 x 192 12.6 and 15.5;
+    //   not at 4608 x 384 x 384, 17.2 and 15.6);
+    //  64 x 64, 8 waves in 2 k groups, up to 700 tiles (2304 x 1152 x 384, 648,
+    //   20.1, 128 x 64 23.1; 2900 x 1152 x 384, 828, 25.9 and 24.4);
+    //  128 x 128, 4 waves, from 384 tiles (5000 x 1536 x 384, 480, 43.8, 128 x 64
+    //   47.5; 43200 x 1536 x 384 320 and 350, on FP32 MFMAs 462), and 128 x 64 in
+    //   between (3600 x 1536 x 384, 348 tiles of 128 x 128, 37.3 and 41.5)
+    const long long gm64 = cdiv(a.M, 64);
+    const long long t6432 = gm64 * (a.N / 32), t6464 = gm64 * (a.N / 64), t12864 = (long long)gm * (a.N / 64);
+    const long long t128 = a.N % 128 == 0 ? (long long)gm * (a.N / 128) : 0;
+    const long long t3232 = (long long)cdiv(a.M, 32) * (a.N / 32);
+    if (t3232 <= 256 && a.K % 64 == 0)
+      gemm_f32_kernel<32, 32, 1, 1, 4, 64, 2, EPI><<<(unsigned)t3232, 256, 0, s>>>(a);
+    else if (t6432 <= 256 && a.K % 64 == 0)
+      gemm_f32_kernel<64, 32, 2, 1, 4, 64, 2, EPI><<<(unsigned)t6432, 512, 0, s>>>(a);
+    else if (t6464 <= 700 && !(t12864 >= 160 && t12864 <= 256))
+      gemm_f32_kernel<64, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t6464, 512, 0, s>>>(a);
+    else if (t128 >= 384)
+      gemm_f32_kernel<128, 128, 2, 2, 1, 32, 1, EPI><<<(unsigned)t128, 256, 0, s>>>(a);
+    else
+      gemm_f32_kernel<128, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t12864, 512, 0, s>>>(a);
+    return hipGetLastError() == hipSuccess ? 0 : -5;
   } else {
-    if constexpr (XM == X_DENSE && sizeof(typename Op::T) == 4) {
-      // Five tile forms, by how many tiles they give the 256 CUs, each with a
-      // shape's us in it and in its neighbour (M x N x K; captured launches on
-      // one card):
-      //  32 x 32, 4 waves in 4 k groups, while its tiles are at most one per CU:
-      //   latency counts, and a workgroup reads a third less than a 64 x 32 one
-      //   (576 x 384 x 1536, 216 tiles, 15.5 and 18.6; on FP32 MFMAs 55.7; 800 x
-      //   384 x 1536, 300 tiles, 20.5 and 18.8);
-      //  64 x 32, 8 waves in 4 k groups, while its tiles are at most one per CU
-      //   (448 x 1152 x 384, 252 tiles, 7.8, 64 x 64 9.5; 576 x 1152 x 384, 324
-      //   tiles, 10.5 and 9.7);
-      //  128 x 64, 8 waves in 2 k groups, from 160 to 256 tiles, about one per CU
-      //   (1152 x 1152 x 384 13.5, 64 x 64 13.9; 10800 x 192 x 192 12.6 and 15.5;
-      //   not at 4608 x 384 x 384, 17.2 and 15.6);
-      //  64 x 64, 8 waves in 2 k groups, up to 700 tiles (2304 x 1152 x 384, 648,
-      //   20.1, 128 x 64 23.1; 2900 x 1152 x 384, 828, 25.9 and 24.4);
-      //  128 x 128, 4 waves, from 384 tiles (5000 x 1536 x 384, 480, 43.8, 128 x 64
-      //   47.5; 43200 x 1536 x 384 320 and 350, on FP32 MFMAs 462), and 128 x 64 in
-      //   between (3600 x 1536 x 384, 348 tiles of 128 x 128, 37.3 and 41.5)
-      const long long gm64 = cdiv(a.M, 64);
-      const long long t6432 = gm64 * (a.N / 32), t6464 = gm64 * (a.N / 64), t12864 = (long long)gm * (a.N / 64);
-      const long long t128 = a.N % 128 == 0 ? (long long)gm * (a.N / 128) : 0;
-      const long long t3232 = (long long)cdiv(a.M, 32) * (a.N / 32);
-      if (t3232 <= 256 && a.K % 64 == 0)
-        gemm_f32_kernel<32, 32, 1, 1, 4, 64, 2, EPI><<<(unsigned)t3232, 256, 0, s>>>(a);
-      else if (t6432 <= 256 && a.K % 64 == 0)
-        gemm_f32_kernel<64, 32, 2, 1, 4, 64, 2, EPI><<<(unsigned)t6432, 512, 0, s>>>(a);
-      else if (t6464 <= 700 && !(t12864 >= 160 && t12864 <= 256))
-        gemm_f32_kernel<64, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t6464, 512, 0, s>>>(a);
-      else if (t128 >= 384)
-        gemm_f32_kernel<128, 128, 2, 2, 1, 32, 1, EPI><<<(unsigned)t128, 256, 0, s>>>(a);
-      else
-        gemm_f32_kernel<128, 64, 2, 2, 2, 32, 2, EPI><<<(unsigned)t12864, 512, 0, s>>>(a);
-      return hipGetLastError() == hipSuccess ? 0 : -5;
-    }
     // the gather loader's per-row token coordinates leave no registers for a
     // 128-wide tile with two prefetched stages
     if constexpr (XM == X_DENSE) {
