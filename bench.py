@@ -199,9 +199,8 @@ def attention_only_bench(log, iters=10):
     vt = torch.randn(heads, 64, ld, device="cuda").to(torch.bfloat16)
     o = torch.zeros(ntok, heads * 64, device="cuda", dtype=torch.bfloat16)
     assert q.shape == (heads, ld, 64) and vt.shape == (heads, 64, ld) and ld >= ntok + 64 and ld % 16 == 0
-    # the entry point without allocations: its request descriptor and work
-    # list are written by a small kernel on the stream, so nothing on the host
-    # (no allocation, copy or synchronisation) sits between the timed launches
+    # the entry point that only enqueues: nothing on the host (no allocation,
+    # copy or synchronisation) sits between the timed launches
     call = lambda: lib.revo_op_attention_noalloc(1, q.data_ptr(), k.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, ntok,
                                                  ld, None)
     assert call() == 0

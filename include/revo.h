@@ -51,7 +51,10 @@ enum revo_status {
 };
 
 enum revo_precision {
-  REVO_FP32 = 0,  /* FP32 operands and accumulation */
+  REVO_FP32 = 0,  /* FP32 operands over their whole range and FP32 accumulation; of every product
+                     of two values the part below 2^-24 of it is left out (sums of a few nonzero
+                     products are off by up to 2.4 units of 2^-24, longer ones by less than with
+                     FP32 products) */
   REVO_BF16 = 1,  /* BF16 operands, FP32 accumulation, FP32 residual/LN/softmax/composite */
   REVO_FP8 = 2    /* OCP FP8 E4M3 operands for the block products (qkv, proj, fc1, fc2) and the
                      encoder-to-decoder projection, with per-output-row weight scales and

@@ -727,12 +727,13 @@ __device__ __forceinline__ void attn_f32_tile(const AttnArgs& a, const AttnItem&
 }
 
 // One workgroup per work entry and head.  What bounds it at full load is the
-// matrix cores: 6 heads of 10800 tokens take 916 us, 196 TFLOP/s of FP32 work
-// or 1172 TFLOP/s of BF16 products (FP32 MFMAs: 1371 us); 6 heads of 3600
-// tokens, 174 workgroups on 256 CUs, 247 -> 141 us; 6 heads of 576 43.7 ->
-// 17.3 us, three rounds of a wave's block at 3.3 us, its splits and products
-// one after the other.  Errors against 64 bits fall from 1.3e-6 to 9.2e-7 relative at 3600
-// tokens and from 2.1e-6 to 1.2e-6 at 10800.
+// matrix cores: 6 heads of 10800 tokens take 921 us, 195 TFLOP/s of FP32 work or
+// 1170 TFLOP/s of BF16 products (FP32 MFMAs: 1357 us); 6 heads of 3600 tokens,
+// 174 workgroups on 256 CUs, 243 -> 139 us; 6 heads of 576 42.7 -> 17.2 us, three
+// rounds of a wave's block at 3.3 us, its splits and products one after the
+// other.  Errors against 64 bits, relative rms, FP32 MFMAs first: 1.35e-6 and
+// 8.1e-7 at 3600 tokens, 7.6e-7 and 4.8e-7 at 576, 2.0e-7 and 1.5e-7 at 8; two
+// tokens 8.2e-8 and 9.2e-8.
 __global__ __launch_bounds__(F32_NT, 2) void attn_f32_kernel(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[F32_LDS];
   AttnItem it;

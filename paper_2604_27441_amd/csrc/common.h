@@ -90,8 +90,12 @@ __device__ inline float to_float(__bf16 x) { return (float)x; }
 __device__ inline int acc_row(int i, int lane) { return (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3); }
 
 // split3: exact split of two floats into three BF16 parts each, x = p0 + p1 +
-// p2 with every part the nearest BF16 to what is left (|p1| <= 2^-9 |x|, |p2|
-// <= 2^-18 |x|; 24 bits of mantissa are 8 + 8 + 8); part j of the two in pj.
+// p2 with every part the nearest BF16 to what is left (24 bits of mantissa are 8
+// + 8 + 8); part j of the two in pj.  A BF16 of exponent e is a multiple of
+// 2^(e-7), so what is left after p0 is at most 2^(e-8): |p1| <= 2^-8 |x|, and
+// what is left of that, a power of two lower unless it is p1 itself, |p2| <=
+// 2^-17 |x|.  Of the nine products of two splits the three smallest, p1 p2, p2
+// p1 and p2 p2, are together at most (2^-24 + 2^-34) of the whole.
 // split3x4: four floats times 2^24, part j of the four in p[j].  The scale
 // keeps every part out of the subnormal range, which the BF16 MFMA flushes.
 __device__ inline uint32_t bf16_pack(float a, float b) {

@@ -70,10 +70,12 @@ __device__ inline float erf_as(float x) {
 }
 
 // GELU(v) = v Phi(v) as v / (1 + 2^(-v q(v^2))): v q(v^2) is the log2 odds of
-// Phi(v), q its minimax polynomial for the error of v Phi(v) on |v| <= 7 (6.7e-8;
-// beyond, q stays positive and growing, so the result tends to v or 0).  10
-// plain and 2 transcendental instructions per value; v times an erf by A&S
-// 7.1.26 takes 13 and 2 with an error of 2.1e-7.
+// Phi(v), log2(Phi(v) / Phi(-v)).  q is the polynomial of degree 6 whose largest
+// error of v Phi(v) on 0 < v <= 7 is least, to first order: the error of q times
+// v^2 Phi (1 - Phi) ln 2, minimised as a linear program over the coefficients
+// and that bound.  6.7e-8; beyond 7, q stays positive and growing, so the result
+// tends to v or 0.  10 plain and 2 transcendental instructions per value; v
+// times an erf by A&S 7.1.26 takes 13 and 2 with an error of 2.1e-7.
 __device__ inline float gelu_erf(float v) {
   const float u = v * v;
   const float q = fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, 5.209905619e-9f, -3.850448520e-7f), 1.145242752e-5f),
@@ -902,15 +904,18 @@ __global__ __launch_bounds__(64 * WM_* WN_, OCC) void gemm_dma_kernel(const Gemm
 // ---------------------------------------------------------------------------
 // Dense FP32 form on the BF16 matrix cores.  An FP32 value is exactly the sum
 // of three BF16 values (common.h split3), and the six largest of the nine
-// products of two such triples (all but x2 w3, x3 w2 and x3 w3, together at
-// most 2^-26 of |x w|) go into FP32 accumulators: 6 products at 16 times the
-// rate of the FP32 MFMA.  What bounds it at large sizes is the matrix cores:
+// products of two such triples (all but p1 p2, p2 p1 and p2 p2) go into FP32
+// accumulators: 6 products at 16 times the rate of the FP32 MFMA.  What bounds it at large sizes is the matrix cores:
 // 171 - 179 TFLOP/s at 43200 rows are 1030 - 1070 TFLOP/s of BF16 products,
 // where a large BF16 product of the library reaches 1263 (FP32 MFMA: 114 -
-// 125 TFLOP/s before, 154 for a large library product).  Its error against 64
-// bits is no larger: 2.9e-7 relative (K = 384) and 6.0e-7 (1536) with one k
-// group, 3.5e-7 and 7.0e-7 before; with two groups 2.1e-7 and 4.2e-7, 2.5e-7
-// and 5.0e-7 before.  Operand stages of BK values per row are fetched into
+// 125 TFLOP/s before, 154 for a large library product).  Six products take 16 of
+// K, where the FP32 MFMA takes 2 at a time, so a sum rounds less often, and what
+// is left out stays below that: relative rms against 64 bits, FP32 MFMAs first,
+// K = 384 3.5e-7 and 2.9e-7 with one k group, 2.5e-7 and 1.5e-7 with four; K =
+// 1536 5.0e-7 and 4.2e-7 with two, 3.0e-7 with four; K = 32 8.3e-8 and 5.1e-8.
+// Sums of fewer than some 16 nonzero products are the exception: of one product
+// 2.5e-8 and 3.5e-8 (at most 1.0 and 2.4 of 2^-24), of four in K = 384 4.0e-8
+// and 7.4e-8.  Of values of at most 16 significant bits nothing is left out.  Operand stages of BK values per row are fetched into
 // registers two stages ahead, split once per element on the way into LDS (one
 // BF16 plane per part), and read from there as 16-byte fragments.
 //

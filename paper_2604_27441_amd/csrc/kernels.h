@@ -78,9 +78,13 @@ constexpr int ATTN_MAX_OP_HEADS = 64;  // heads of a launch whose E8M0 exponents
 // tiles whose waves split the keys six ways while six heads of them are at most
 // one workgroup per CU (us for 6 heads, 128-query tiles first: 576 tokens 28.8
 // and 17.3, 1024 tokens 45 and 27, 1300 tokens 54 and 33, 1500 tokens 61 and 65).
-// The rule looks at the request alone, so that its result is the same in every
-// batch; launches that know all of their work (AttnArgs::tile) ask whether all
-// their tiles are (24 heads of 576 tokens: 31 and 35).
+// The rule looks at the request alone, because the work list and the kernel of a
+// captured launch must agree on it for whatever batch a replay brings; launches
+// that know all of their work (AttnArgs::tile) ask whether all their tiles are
+// (24 heads of 576 tokens: 31 and 35, 43 on FP32 MFMAs).  A captured launch is
+// sized for 32-query tiles throughout; its empty workgroups cost nothing that
+// shows (one 256x192 request in a graph for 5400 tokens: 17.7 us a launch, 18.6
+// without a graph).
 __host__ __device__ inline int attn_tile(Prec p, int N) { return p == P_FP32 && N <= 1344 ? 32 : 128; }
 inline int attn_tile_all(Prec p, int N, int heads) {
   return p == P_FP32 && (long long)heads * cdiv(N, 32) <= 256 ? 32 : 128;
