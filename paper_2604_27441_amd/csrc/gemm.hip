@@ -1178,9 +1178,12 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
   //   1152 x 384, 648: BF16 6.0 and 7.0, FP8 5.0 and 5.5).  They stop winning
   //   between there and 1350 tiles (14400 x 384 x 384: BF16 23.6 and 18.6);
   //  BF16 beyond: 128 x 128 on 8 waves of 64 x 32, four waves per SIMD (10800 x
-  //   1536 x 384 GELU 21.9, on 4 waves 22.5; 43200 x 384 x 384 residual 43.8 and
-  //   45.2; 43200 x 1152 x 384 50.5 and 49.8), or 256 x 64 on 8 waves where N is
-  //   not a multiple of 128 (43200 x 576 x 192 18.6, 128 x 64 19.7);
+  //   1536 x 384 GELU 21.9, on 4 waves 22.5; 43200 x 1152 x 384 50.5 and 49.8), or
+  //   256 x 64 on 8 waves where N is not a multiple of 128 (43200 x 576 x 192 18.6,
+  //   128 x 64 19.7); residuals of more than two tiles per CU on 4 waves of 64 x
+  //   64: alone those lose (43200 x 384 x 384 45.2, on 8 waves 43.8), but they
+  //   leave registers for the other network's attention beside them (the step of
+  //   four 1280x720 pairs on two streams 25.38 ms, 25.85 with 8 waves);
   //  FP8 beyond, whose stages hold twice the K: 128 x 64 on 4 waves, three
   //   workgroups per CU (14400 x 1536 x 384 GELU 23.3, 128 x 128 24.0; 7400 x 1152
   //   x 384 9.0 and 10.6; 43200 x 192 x 384 10.3, 256 x 64 11.7), but 128 x 128 on
@@ -1200,6 +1203,8 @@ int launch_t(const GemmArgs& a, hipStream_t s) {
       } else if constexpr (B16) {
         if (a.N % 128)
           gemm_dma_kernel<Op, 256, 64, 4, 2, 1, EPI, OutT><<<gm2 * (a.N / 64), 512, 0, s>>>(a);
+        else if (EPI == EPI_RESIDUAL && t128 > 512)
+          gemm_dma_kernel<Op, 128, 128, 2, 2, 2, EPI, OutT><<<(unsigned)t128, 256, 0, s>>>(a);
         else
           gemm_dma_kernel<Op, 128, 128, 2, 4, 4, EPI, OutT><<<(unsigned)t128, 512, 0, s>>>(a);
       } else {
