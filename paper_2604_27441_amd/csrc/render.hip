@@ -75,7 +75,7 @@ __device__ __forceinline__ bool project_point(const float4& p, unsigned n, const
 // The box costs a wave two more barriers and a pass over its pixels, so a wave
 // whose atomics are cheap already sends its points itself: those whose points,
 // per lane, continue on their left neighbour's line and rarely on its very
-// pixel (atomics on one pixel take turns).  Frames of 400 000 points or fewer
+// pixel (atomics on one pixel take turns).  Calls of 400 000 points or fewer
 // never fill the chip, so they take one row per wave, count no lines and box
 // only points that collide.  us with an atomic per point, with a box for every
 // tile of 64 x 16, and as it is (captured launches; the view is 100 mm aside and 5
@@ -83,12 +83,14 @@ __device__ __forceinline__ bool project_point(const float4& p, unsigned n, const
 // unmoved 44, 48, 43, at half size 83, 28, 29, a tenth of the points valid 34.6,
 // 39.5, 33.8, depth all noise 91, 80, 75; one 640x480 frame 11.7, 12.0, 11.6,
 // unmoved 8.9, 10.9, 9.0, 6 m back 21.6, 11.8, 15.4; one 256x192 frame 6.1, 8.7,
-// 6.2.  Behind the atomic per point by 5 to 8 %: one unmoved 1280x720 frame 14.0,
+// 6.2.  Behind the atomic per point by 4 to 12 %: one unmoved 1280x720 frame 14.0,
 // 16.3, 14.7, two 640x480 frames of patches of a fifth of the points 11.3, 13.5,
-// 12.1, four frames of much missing depth 400 mm nearer 40.6, 46.2, 42.6.
+// 12.1, one 1280x720 frame of a few bands of rows 10.3, 13.3, 11.5, four frames of
+// much missing depth 400 mm nearer 40.6, 46.2, 42.6.  (12 to 20 for a lone frame's
+// MAX_SAME give 11.3 to 13.4 from 6 m back, but 6.4 to 6.6 for the 256x192 frame.)
 // The minimum is the same by every way.  16 KB of LDS leave 8 workgroups per CU.
 constexpr int SW = 64, SBOX = 2048;
-constexpr long long SMALL_SPLAT = 400000;  // points
+constexpr long long SMALL_SPLAT = 400000;  // points of all frames of a call
 template <int SPT>
 __global__ __launch_bounds__(RT) void splat_kernel(const float4* __restrict__ pts, int H, int W, Pose P, Intr k,
                                                    int Ho, int Wo, unsigned long long* __restrict__ zbuf) {

@@ -160,7 +160,7 @@ def test_zoomed_view(zoom, H, W):
         assert np.array_equal(w[b], rw) and np.array_equal(c[b], rc) and np.array_equal(d[b], rd)
 
 
-# frames of at most 400 000 points (one row per wave) and of more (two)
+# calls of at most 400 000 points (one row per wave) and of more (two)
 @pytest.mark.parametrize("B,H,W", [(2, 35, 130), (2, 330, 611)])
 @pytest.mark.parametrize("zoom", [8.0, 2.0, 1.0, 0.5, 0.25])
 def test_zoomed_view_of_mixed_rows(B, H, W, zoom):
